@@ -129,7 +129,7 @@ __device__ __forceinline__ void interface_flux_vjp(R hm, R um, R vm, R bm, R hp,
 struct AdjArgs {
     Mesh<double> m;
     Phys<double> P;
-    Tab<double> tab;               // uniform entries
+    Uni<double> tab;               // uniform entries
     const Tab<double> *tg;         // the same in device memory (per-lane entries)
     const double *h, *hu, *hv;     // stage input W_{k-1}
     const double *a[3];            // dL/dW_k (nullptr: zero)
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(Shape<N>::T, AdjWaves<N>::value) void adjoint_stage
     s_a[t] = double2{Ax, Cx};
     s_b[t] = double2{Ae, Ce};
     s_m[0][t] = m0; s_m[1][t] = m1; s_m[2][t] = m2;
-    for (int c = t; c < nf * nf; c += T) s_dz[c] = a.tg->Dz[(c / nf) * kMaxNF + (c - (c / nf) * nf)];
+    for (int c = t; c < nf * nf; c += T) s_dz[c] = a.tg->Dz[c];
     lds_sync<T>();
 
     // ---- interface: own term w.r.t. the '-' trace, neighbour's term w.r.t. its '+' trace ----

@@ -106,7 +106,7 @@ hipError_t Launch<N, R>::indicator(const Bufs &B, int buf, const Phys<R> &P, con
 {
     IndicatorArgs<N, R> a;
     a.P = P;
-    a.tab = t;
+    a.tab = uniform_entries(t, N);
     a.tg = (const Tab<R> *)B.tabg;
     a.K = B.K;
     a.h = (const R *)B.W[buf][0];
@@ -124,7 +124,7 @@ static ListArgs<N, R> list_args(const Bufs &B, int in, const Phys<R> &P, const T
     ListArgs<N, R> a;
     a.m = mesh_view<R>(B);
     a.P = P;
-    a.tab = t;
+    a.tab = uniform_entries(t, N);
     a.tg = (const Tab<R> *)B.tabg;
     a.h = (const R *)B.W[in][0];
     a.hu = (const R *)B.W[in][1];
@@ -190,7 +190,7 @@ hipError_t Launch<N, R>::stage(const Bufs &B, const StageCall &c, const Phys<R> 
     StageArgs<R> a;
     a.m = mesh_view<R>(B);
     a.P = P;
-    a.tab = t;
+    a.tab = uniform_entries(t, N);
     a.tg = (const Tab<R> *)B.tabg;
     a.h = (const R *)B.W[c.in][0];
     a.hu = (const R *)B.W[c.in][1];
@@ -235,7 +235,7 @@ template <int N, typename R>
 hipError_t Launch<N, R>::limit(const Bufs &B, int buf, const Phys<R> &P, const Tab<R> &t, hipStream_t s)
 {
     hipLaunchKernelGGL((limit_kernel<N, R>), tile_grid<N>(B.K), dim3(Shape<N>::T), 0, s, mesh_view<R>(B), P,
-                       t, (R *)B.W[buf][0], (R *)B.W[buf][1], (R *)B.W[buf][2], B.flags, ntiles_of<N>(B.K));
+                       uniform_entries(t, N), (R *)B.W[buf][0], (R *)B.W[buf][1], (R *)B.W[buf][2], B.flags, ntiles_of<N>(B.K));
     return hipGetLastError();
 }
 
@@ -279,7 +279,7 @@ hipError_t Launch<N, R>::diag(const Bufs &B, int buf, const Phys<R> &P, const Ta
     const int64_t nb = (B.K * np + T - 1) / T;
     *nblocks = nb;
     if (nb > B.part_cap) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((diag_kernel<N, R>), dim3((unsigned)nb), dim3(T), 0, s, mesh_view<R>(B), P, t,
+    hipLaunchKernelGGL((diag_kernel<N, R>), dim3((unsigned)nb), dim3(T), 0, s, mesh_view<R>(B), P, uniform_entries(t, N),
                        (const R *)B.W[buf][0], (const R *)B.W[buf][1], (const R *)B.W[buf][2],
                        (const R *)B.b, (const R *)B.Rb[0], (const R *)B.Rb[1], (const R *)B.Rb[2], B.part);
     return hipGetLastError();
@@ -293,7 +293,7 @@ hipError_t Launch<N, R>::adjoint_stage(const Bufs &B, const AdjCall &c, const Ph
         AdjArgs a;
         a.m = mesh_view<double>(B);
         a.P = P;
-        a.tab = t;
+        a.tab = uniform_entries(t, N);
         a.tg = (const Tab<double> *)B.tabg;
         a.h = (const double *)c.W[0];
         a.hu = (const double *)c.W[1];

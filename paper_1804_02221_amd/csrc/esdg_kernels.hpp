@@ -123,6 +123,20 @@ __device__ __forceinline__ void lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// The kernel's one argument, a struct A, read where it lies (the kernarg
+// segment) instead of through the parameter: a parameter's fields are all
+// loaded at the kernel's entry and held, which with some forty pointers and
+// the operator tables spills scalar registers.  Each call of kernarg starts
+// afresh: fields read through its result are loaded behind the call, and
+// need not live from one phase of the kernel to the next.
+template <typename A>
+__device__ __forceinline__ const A &kernarg()
+{
+    auto p = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const A *)p;
+}
+
 constexpr int kXcds = 8;
 constexpr int kDtSlots = 64;
 
@@ -155,14 +169,37 @@ __device__ __forceinline__ void side_node(int s, int k, int &i, int &j)
 // ------------------------------------------------------------------------
 // Arguments
 // ------------------------------------------------------------------------
+// Operator tables of one degree, in device memory.
 template <typename R>
 struct Tab {
     R D[kMaxNF * kMaxNF];     // derivative matrix, row-major
-    R Dz[kMaxNF * kMaxNF];    // the same with a zero diagonal (flux differencing)
-    R Vinv[kMaxNF * kMaxNF];  // Vandermonde inverse
+    R Dz[kMaxNF * kMaxNF];    // the same with a zero diagonal (flux differencing), rows of N + 1
+    R Vinv[kMaxNF * kMaxNF];  // Vandermonde inverse, rows of N + 1
     R w[kMaxNF];              // LGL weights
     R iw0;                    // 1 / w_0 (end weight)
 };
+
+// The entries that kernels read as scalars, passed by value.
+template <typename R>
+struct Uni {
+    R w[kMaxNF];              // LGL weights
+    R ve[kMaxNF], vo[kMaxNF]; // rows of Vinv: the even and the odd one of modes N and N - 1
+    R iw0;                    // 1 / w_0
+};
+
+template <typename R>
+inline Uni<R> uniform_entries(const Tab<R> &t, int N)
+{
+    Uni<R> u;
+    const int e = N & 1 ? N - 1 : N, o = N & 1 ? N : N - 1;
+    for (int k = 0; k < kMaxNF; ++k) {
+        u.w[k] = k <= N ? t.w[k] : R(0);
+        u.ve[k] = k <= N ? t.Vinv[e * (N + 1) + k] : R(0);
+        u.vo[k] = k <= N ? t.Vinv[o * (N + 1) + k] : R(0);
+    }
+    u.iw0 = t.iw0;
+    return u;
+}
 
 template <typename R>
 struct Mesh {
@@ -206,6 +243,7 @@ struct Phys {
     R i2g;                 // 1 / (2 g)
     R ratio_min, ratio_max; // 10^sigma_min, 10^sigma_max
     R visc_c, br1;          // viscous bound: visc_c / (br1 eps max|grad|^2)
+    R smooth_tau;           // threshold of smooth_line (0: no line is taken to be smooth)
     int ec, limiter_on;
 };
 
@@ -548,6 +586,21 @@ __device__ __forceinline__ bool block_any(bool pred)
     else return __syncthreads_or(pred) != 0;
 }
 
+// The same through flag, T/64 ints of LDS used for nothing else: one barrier
+// that does not wait for global stores, as __syncthreads_or() would.
+template <int T>
+__device__ __forceinline__ bool block_any_lds(bool pred, int *flag, int t)
+{
+    const bool mine = __ballot(pred) != 0ull;
+    if constexpr (T == 64) return mine;
+    if ((t & 63) == 0) flag[t >> 6] = mine;
+    lds_sync<T>();
+    int any = 0;
+#pragma unroll
+    for (int w = 0; w < T / 64; ++w) any |= flag[w];
+    return any != 0;
+}
+
 // ------------------------------------------------------------------------
 // Workgroup-level per-element reductions over the nodes of each element.
 // red: LDS scratch of T*NQ reals; returns the element total in every thread.
@@ -695,6 +748,68 @@ __device__ __forceinline__ R viscosity_from_totals(R all, R top, R allM, R topM,
            (R(1) + sin(R(3.14159265358979323846) * (sg - R(0.5) * (smax + smin)) / (smax - smin)));
 }
 
+// Is nodal line l (l < 2(N+1): the lines of the two directions) of an
+// element whose heights sit at sh[i*(N+1) + j] certainly smooth?  An element
+// with 2(N+1) smooth lines has no viscosity, so that the modal transform of
+// element_viscosity is only needed where some line is not smooth.
+//
+// With c_j the coefficient of mode N of xi-line j and d_i that of eta-line i,
+// the top shell's energy is at most the sum over both sets of lines of their
+// squared L2 norms along the other direction, hence at most sum_j w_j c_j^2 +
+// sum_i w_i d_i^2 (the LGL rule overestimates squares of degree N).  The
+// energy of all modes is at least (N / (2N+1))^2 sum_ij w_i w_j h_ij^2 (it
+// overestimates by at most 2 + 1/N per direction), and sum_r w_r h_r^2 on a
+// line is at least half the square of m = sum_r w_r h_r.  So c^2 <= tau m^2
+// on every line, with 2 tau = 0.99 x (N / (2N+1))^2 / 2 x 10^sigma_min x (1 -
+// 10^sigma_min), keeps the top shell's share below 10^sigma_min, and the same
+// for mode N - 1 keeps shell N - 1's share of the modes up to N - 1 below it:
+// the exact test of viscosity_from_totals would give zero too.  tau = 0
+// (thresholds near rounding, see phys()) leaves every element to that test.
+//
+// Per line N+1 LDS reads and 2(N+1) + 10 operations on 2(N+1) lanes, against
+// 4(N+1) reads, 2(N+1) multiply-adds and three reductions on every lane for
+// the transform, with which the epilogue was bound by LDS and its barriers.
+// Stage kernel on a smooth flow, with the late arguments through kernarg(): 571 -> 541 us at N = 7,
+// 512^2 (float32, 384^2: 214 -> 192 us), 107 -> 91 us at N = 5, 255^2, 152 ->
+// 139 us at N = 2, 601^2.  Tiles at wet/dry fronts pay for both tests: 23.2 ->
+// 23.1 us on a 200^2, N = 3 mesh of which a twentieth is such.
+template <int N, typename R>
+__device__ __forceinline__ bool smooth_line(const R *sh, int l, const Uni<R> &tab, R tau)
+{
+    constexpr int nf = N + 1;
+    const int o = l < nf ? l : (l - nf) * nf, st = l < nf ? nf : 1;
+    // the nodes and modes are symmetric: even modes from the sums of mirrored
+    // nodes, odd ones from their differences
+    constexpr int half = nf / 2;
+    constexpr bool odd = (N & 1) != 0;
+    R m = 0, ce = 0, co = 0;   // mean, even and odd mode of N and N - 1
+    const R mid = odd ? sh[o] : sh[o + half * st];
+    // (the even mode's sum over jumps from one node: no rounding at the size
+    // of h itself, which single precision would see)
+#pragma unroll
+    for (int r = 0; r < half; ++r) {
+        const R a = sh[o + r * st], b = sh[o + (N - r) * st];
+        m += tab.w[r] * (a + b);
+        ce += tab.ve[r] * ((a - mid) + (b - mid));
+        co += tab.vo[r] * (a - b);
+    }
+    if constexpr (!odd) m += tab.w[half] * mid;
+    const R lim = tau * m * m;
+    return ce * ce <= lim && co * co <= lim;
+}
+
+// Lane t's line of a tile of E elements, node (i, j) of element el at
+// sh[el*np + i*(N+1) + j]: true if the element needs element_viscosity.
+template <int N, typename R, int E>
+__device__ __forceinline__ bool rough_line(const R *sh, int t, const Uni<R> &tab, const Phys<R> &P)
+{
+    constexpr int nf = N + 1, np = nf * nf;
+    if (!(P.smooth_tau > R(0))) return true;
+    if (t >= E * 2 * nf) return false;
+    const int el = t / (2 * nf);
+    return !smooth_line<N, R>(sh + el * np, t - el * 2 * nf, tab, P.smooth_tau);
+}
+
 // Element viscosity of the elements whose nodal water heights are staged in
 // sh[el*np + p]: modal coefficients Q^ = V^{-1} h V^{-T}, the energy
 // fractions of the top two mode shells, sigma = log10 of the larger, and the
@@ -752,7 +867,7 @@ template <int N, typename R, int T>
 __device__ __forceinline__ void stage_vinv(R *dst, const Tab<R> &tab, int t)
 {
     constexpr int nf = N + 1;
-    for (int q = t; q < nf * nf; q += T) dst[q] = tab.Vinv[(q / nf) * kMaxNF + (q - (q / nf) * nf)];
+    for (int q = t; q < nf * nf; q += T) dst[q] = tab.Vinv[q];
 }
 
 // Viscous physical fluxes at node (i,j) of the element whose u, v are in
@@ -799,7 +914,7 @@ __device__ __forceinline__ void viscous_flux_at(int i, int j, const R *su, const
 template <int N, typename R>
 struct IndicatorArgs {
     Phys<R> P;
-    Tab<R> tab;                  // uniform entries (read as scalars)
+    Uni<R> tab;                  // uniform entries (read as scalars)
     const Tab<R> *tg;            // the same tables in device memory: per-lane entries
     int64_t K;
     const R *h;
@@ -815,6 +930,7 @@ __global__ __launch_bounds__(Shape<N>::T) void indicator_kernel(IndicatorArgs<N,
     using S = Shape<N>;
     constexpr int np = S::np, E = S::E, T = S::T;
     __shared__ R s_h[T], s_red[6 * T], s_vinv[(N + 1) * (N + 1)];
+    __shared__ int s_any[T / 64];
     const int64_t tile = xcd_tile(a.ntiles);
     if (tile < 0) return;
     const int t = threadIdx.x;
@@ -826,7 +942,9 @@ __global__ __launch_bounds__(Shape<N>::T) void indicator_kernel(IndicatorArgs<N,
     const R h = act ? a.h[e * np + p] : R(0);
     s_h[t] = h;
     lds_sync<T>();
-    const R eps = element_viscosity<N, R>(s_h, s_red, s_vinv, a.P, t, el, p, lane, h);
+    R eps = R(0);
+    if (block_any_lds<T>(rough_line<N, R, E>(s_h, t, a.tab, a.P), s_any, t))
+        eps = element_viscosity<N, R>(s_h, s_red, s_vinv, a.P, t, el, p, lane, h);
     if (act && p == 0) {
         a.eps[e] = eps;
         if (eps > R(0)) a.list[atomicAdd(a.count, 1)] = (int32_t)e;
@@ -839,7 +957,7 @@ template <int N, typename R>
 struct ListArgs {
     Mesh<R> m;
     Phys<R> P;
-    Tab<R> tab;                  // uniform entries (read as scalars)
+    Uni<R> tab;                  // uniform entries (read as scalars)
     const Tab<R> *tg;            // the same tables in device memory: per-lane entries
     const R *h, *hu, *hv;     // stage input state
     const R *eps;             // [K] viscosity of this state
@@ -1052,7 +1170,7 @@ template <typename R>
 struct StageArgs {
     Mesh<R> m;
     Phys<R> P;
-    Tab<R> tab;                  // uniform entries (read as scalars)
+    Uni<R> tab;                  // uniform entries (read as scalars)
     const Tab<R> *tg;            // the same tables in device memory: per-lane entries
     const R *h, *hu, *hv;        // stage input W
     const R *h0, *hu0, *hv0;     // SSP: W^n
@@ -1140,7 +1258,7 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
     R *const s_h = s_st + 8 * LEN;
     __shared__ R s_fl[3][NF];
     __shared__ R s_lim[4 * E];
-    __shared__ R s_vinv[nf * nf];       // V^{-1} for the indicator epilogue (with AV)
+    __shared__ int s_any[2][T / 64];    // block_any_lds
     __shared__ R s_dz[nf * nf];         // D with a zero diagonal (volume term)
     __shared__ R s_mref[kMetricRel<R> ? 4 * E : 1];  // the tile elements' Mesh::mref (single precision)
 
@@ -1223,11 +1341,10 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
     }
     s_a[st] = V2{Ax, Cx};
     s_b[st] = V2{Ae, Ce};
-    if constexpr (MODE != kModeRhs)
-        if (av) stage_vinv<N, R, T>(s_vinv, *a.tg, t);
     // the per-lane table entries of the volume term from LDS rather than
     // through the vector memory path (3-6% faster)
-    for (int c = t; c < nf * nf; c += T) s_dz[c] = a.tg->Dz[(c / nf) * kMaxNF + (c - (c / nf) * nf)];
+    static_assert(nf * nf <= T, "one table entry per lane");
+    if (t < nf * nf) s_dz[t] = a.tg->Dz[t];
     lds_sync<T>();
 
     // ---- interface: (1/w_0) J^surf F*(own, nbr, n_out) per face node; for
@@ -1427,43 +1544,48 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
     const R J = Ce * Ax - Cx * Ae;
 
     // ---- R = (1/J)(-L + S + L^v), S = -(g/2) h (b_x, b_y) ----
+    // (the arguments afresh from here on, see kernarg: held from the entry, they
+    // spilled 24-44 scalar registers; read so from the entry, their latency
+    // cost a 128^2 mesh at N = 7 3%)
+    const StageArgs<R> &late = kernarg<StageArgs<R>>();
+    const Phys<R> &PL = late.P;
     R bxv = 0, byv = 0, Lv2 = 0, Lv3 = 0;
     if (act) {
-        bxv = a.m.bx[q]; byv = a.m.by[q];
-        if (av && eps_e > R(0)) { Lv2 = a.lv2[q]; Lv3 = a.lv3[q]; }
+        bxv = late.m.bx[q]; byv = late.m.by[q];
+        if (av && eps_e > R(0)) { Lv2 = late.lv2[q]; Lv3 = late.lv3[q]; }
     }
     const R iJ = act ? rcp_nr(J) : R(0);
-    const R hg = R(0.5) * P.g * h;
+    const R hg = R(0.5) * PL.g * h;
     const R R1 = -L1 * iJ;
     const R R2 = (-L2 - hg * bxv + Lv2) * iJ;
     const R R3 = (-L3 - hg * byv + Lv3) * iJ;
 
     if constexpr (MODE == kModeRhs) {
-        if (act) { a.oh[q] = R1; a.ohu[q] = R2; a.ohv[q] = R3; }
+        if (act) { late.oh[q] = R1; late.ohu[q] = R2; late.ohv[q] = R3; }
         return;
     } else {
-        const R dt = (R)a.dt[a.inst ? 8 * (int64_t)a.inst[act ? e : e0] : 0];
+        const R dt = (R)late.dt[late.inst ? 8 * (int64_t)late.inst[act ? e : e0] : 0];
         R nh, nhu, nhv;
         R d0 = 0, d1 = 0, d2 = 0;
         if constexpr (MODE == kModeLsrk) {
             // the first stage has a_1 = 0: the register is not read
-            if (act && a.ca != R(0)) { d0 = a.dh[q]; d1 = a.dhu[q]; d2 = a.dhv[q]; }
-            d0 = a.ca * d0 + dt * R1;
-            d1 = a.ca * d1 + dt * R2;
-            d2 = a.ca * d2 + dt * R3;
-            nh = h + a.cb * d0; nhu = hu + a.cb * d1; nhv = hv + a.cb * d2;
+            if (act && late.ca != R(0)) { d0 = late.dh[q]; d1 = late.dhu[q]; d2 = late.dhv[q]; }
+            d0 = late.ca * d0 + dt * R1;
+            d1 = late.ca * d1 + dt * R2;
+            d2 = late.ca * d2 + dt * R3;
+            nh = h + late.cb * d0; nhu = hu + late.cb * d1; nhv = hv + late.cb * d2;
         } else {
             R w0 = 0, w1 = 0, w2 = 0;
-            if (act) { w0 = a.h0[q]; w1 = a.hu0[q]; w2 = a.hv0[q]; }
-            nh = a.ca * w0 + a.cb * (h + dt * R1);
-            nhu = a.ca * w1 + a.cb * (hu + dt * R2);
-            nhv = a.ca * w2 + a.cb * (hv + dt * R3);
+            if (act) { w0 = late.h0[q]; w1 = late.hu0[q]; w2 = late.hv0[q]; }
+            nh = late.ca * w0 + late.cb * (h + dt * R1);
+            nhu = late.ca * w1 + late.cb * (hu + dt * R2);
+            nhv = late.ca * w2 + late.cb * (hv + dt * R3);
         }
         // positivity limiter (eq. PosPres) toward the J-weighted means; an
         // element without a negative node keeps theta = 1, so the means are
         // only formed when some element of the workgroup has one
-        if (P.limiter_on && block_any<T>(act && nh < R(0))) {
-            const R wq = act ? J * a.tg->w[i] * a.tg->w[j] : R(0);
+        if (PL.limiter_on && block_any_lds<T>(act && nh < R(0), s_any[0], t)) {
+            const R wq = act ? J * late.tg->w[i] * late.tg->w[j] : R(0);
             R vals[5] = {wq, wq * nh, wq * nhu, wq * nhv, act ? nh : R(3.0e38)};
             elem_totals_any<N, R, 5, true, T>(vals, s_st, t, el, p, lane);
             if (lane && p == 0) {
@@ -1473,13 +1595,13 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
                 if (act && mn < R(0)) {
                     if (mh < R(0)) {
                         th = R(0);
-                        atomicOr(&a.flags[kFlagNegMean], 1);
-                        if (a.iflags) atomicOr(&a.iflags[a.inst ? a.inst[e] : 0], 1);
+                        atomicOr(&late.flags[kFlagNegMean], 1);
+                        if (late.iflags) atomicOr(&late.iflags[late.inst ? late.inst[e] : 0], 1);
                     } else {
                         th = mh / (mh - mn);
                         th = th < R(1) ? th : R(1);
                     }
-                    atomicAdd(&a.flags[kFlagLimited], 1);
+                    atomicAdd(&late.flags[kFlagLimited], 1);
                 }
                 s_lim[4 * el + 0] = th; s_lim[4 * el + 1] = mh;
                 s_lim[4 * el + 2] = mhu; s_lim[4 * el + 3] = mhv;
@@ -1493,14 +1615,14 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
                 nhv = th * (nhv - mhv) + mhv;
             }
         }
-        if (P.limiter_on && nh < P.h_tol) { nhu = R(0); nhv = R(0); }
+        if (PL.limiter_on && nh < PL.h_tol) { nhu = R(0); nhv = R(0); }
         // a non-finite value in any of the three (an infinity or NaN makes
         // their sum non-finite) is reported once per esdg_step
-        if (act && !__builtin_isfinite(nh + nhu + nhv)) atomicOr(&a.flags[kFlagNonFinite], 1);
+        if (act && !__builtin_isfinite(nh + nhu + nhv)) atomicOr(&late.flags[kFlagNonFinite], 1);
         if (act) {
-            a.oh[q] = nh; a.ohu[q] = nhu; a.ohv[q] = nhv;
+            late.oh[q] = nh; late.ohu[q] = nhu; late.ohv[q] = nhv;
             if constexpr (MODE == kModeLsrk) {
-                if (a.store_du) { a.dh[q] = d0; a.dhu[q] = d1; a.dhv[q] = d2; }
+                if (late.store_du) { late.dh[q] = d0; late.dhu[q] = d1; late.dhv[q] = d2; }
             }
         }
         R en = R(0);
@@ -1508,22 +1630,28 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
             // viscosity of the new state for the next stage (appendix A)
             s_st[8 * T + t] = nh;
             lds_sync<T>();
-            en = element_viscosity<N, R, T>(s_st + 8 * T, s_st, s_vinv, P, t, el, p, lane, nh);
+            if (block_any_lds<T>(rough_line<N, R, E>(s_st + 8 * T, t, late.tab, PL), s_any[1], t)) {
+                static_assert(2 * T >= nf * nf, "V^{-1} between the reduction scratch and the heights");
+                R *const s_vinv = s_st + 6 * T;
+                if (t < nf * nf) s_vinv[t] = late.tg->Vinv[t];
+                lds_sync<T>();
+                en = element_viscosity<N, R, T>(s_st + 8 * T, s_st, s_vinv, PL, t, el, p, lane, nh);
+            }
             if (act && p == 0) {
-                a.eps_out[e] = en;
-                if (en > R(0)) a.list_out[atomicAdd(a.count_out, 1)] = (int32_t)e;
+                late.eps_out[e] = en;
+                if (en > R(0)) late.list_out[atomicAdd(late.count_out, 1)] = (int32_t)e;
             }
         }
-        if (a.dtc_out) {
+        if (late.dtc_out) {
             // face records of the new state for the Lemma 2 bounds of the
             // next step: per face node the height and both velocities, the
             // values the time-step pass would read from the state (corner
             // nodes write both sides)
-            if (a.frec_out && act) {
-                const R ihn = rcp_wet(nh, P.h_tol);
+            if (late.frec_out && act) {
+                const R ihn = rcp_wet(nh, PL.h_tol);
                 const R un = nhu * ihn, vn = nhv * ihn;
                 auto rec = [&](int s, int k) {
-                    R *const r = a.frec_out + ((e * 4 + s) * nf + k) * 3;
+                    R *const r = late.frec_out + ((e * 4 + s) * nf + k) * 3;
                     r[0] = nh;
                     r[1] = un;
                     r[2] = vn;
@@ -1534,12 +1662,12 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
                 if (i == 0) rec(3, j);
             }
             // CFL and viscous bounds of the new state for the next step
-            R vals[1] = {act ? cfl_bound<N, R>(nh, nhu, nhv, Ax, Cx, Ae, Ce, J, P) : R(3.0e38)};
+            R vals[1] = {act ? cfl_bound<N, R>(nh, nhu, nhv, Ax, Cx, Ae, Ce, J, PL) : R(3.0e38)};
             lds_sync<T>();   // scratch free
             elem_totals_any<N, R, 1, true, T>(vals, s_st, t, el, p, lane);
             if (act && p == 0) {
-                a.dtc_out[e] = vals[0];
-                if (a.dtv_out) a.dtv_out[e] = en > R(0) ? visc_bound<R>(en, a.gmax[e], P) : R(3.0e38);
+                late.dtc_out[e] = vals[0];
+                if (late.dtv_out) late.dtv_out[e] = en > R(0) ? visc_bound<R>(en, late.gmax[e], PL) : R(3.0e38);
             }
         }
     }
@@ -1549,7 +1677,7 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
 // Standalone limiter (initial data / esdg_limit)
 // ------------------------------------------------------------------------
 template <int N, typename R>
-__global__ __launch_bounds__(Shape<N>::T) void limit_kernel(Mesh<R> m, Phys<R> P, Tab<R> tab, R *h_,
+__global__ __launch_bounds__(Shape<N>::T) void limit_kernel(Mesh<R> m, Phys<R> P, Uni<R> tab, R *h_,
                                                             R *hu_, R *hv_, int *flags, int64_t ntiles)
 {
     using S = Shape<N>;
@@ -1913,7 +2041,7 @@ __global__ __launch_bounds__(kDtThreads) void dt_batch_kernel(DtArgs<R> a)
 // min h, max h, #dry nodes.
 // ------------------------------------------------------------------------
 template <int N, typename R>
-__global__ __launch_bounds__(Shape<N>::T) void diag_kernel(Mesh<R> m, Phys<R> P, Tab<R> tab, const R *h_,
+__global__ __launch_bounds__(Shape<N>::T) void diag_kernel(Mesh<R> m, Phys<R> P, Uni<R> tab, const R *h_,
                                                            const R *hu_, const R *hv_, const R *b_,
                                                            const R *r0, const R *r1, const R *r2,
                                                            double *part)

@@ -386,6 +386,11 @@ Phys<R> phys(const esdg_ctx *c)
     p.ratio_max = (R)std::pow(10.0, c->P.sigma_max);
     p.visc_c = (R)(c->P.cfl_visc * 4.0 * kLsrkRealLimit);
     p.br1 = (c->N >= 2 && c->N <= 8) ? (R)kBR1Radius[c->N] : R(1);
+    // smooth_line's threshold; near the rounding of a line's modes relative
+    // to its mean (squared) no line is taken to be smooth
+    const double k = c->N / (2.0 * c->N + 1.0), rho = std::pow(10.0, c->P.sigma_min);
+    const double tau = 0.99 * 0.25 * k * k * rho * (1.0 - rho);
+    p.smooth_tau = tau > (sizeof(R) == 8 ? 1e-20 : 1e-9) ? (R)tau : R(0);
     p.ec = c->P.surface_flux == 1;
     p.limiter_on = c->P.limiter_on != 0;
     return p;
@@ -978,10 +983,11 @@ int upload_mesh_impl(esdg_ctx *ctx, int N, int64_t K, const double *x, const dou
         for (int j = 0; j <= N; ++j) {
             ctx->td.D[i * kMaxNF + j] = (double)ctx->ht.D[i][j];
             ctx->tf.D[i * kMaxNF + j] = (float)ctx->ht.D[i][j];
-            ctx->td.Dz[i * kMaxNF + j] = i == j ? 0.0 : (double)ctx->ht.D[i][j];
-            ctx->tf.Dz[i * kMaxNF + j] = i == j ? 0.0f : (float)ctx->ht.D[i][j];
-            ctx->td.Vinv[i * kMaxNF + j] = (double)ctx->ht.Vinv[i][j];
-            ctx->tf.Vinv[i * kMaxNF + j] = (float)ctx->ht.Vinv[i][j];
+            const int c = i * (N + 1) + j;
+            ctx->td.Dz[c] = i == j ? 0.0 : (double)ctx->ht.D[i][j];
+            ctx->tf.Dz[c] = i == j ? 0.0f : (float)ctx->ht.D[i][j];
+            ctx->td.Vinv[c] = (double)ctx->ht.Vinv[i][j];
+            ctx->tf.Vinv[c] = (float)ctx->ht.Vinv[i][j];
         }
     }
     Bufs &B = ctx->B;
