@@ -406,8 +406,8 @@ __global__ void bathymetry_adjoint_kernel(int64_t K, const double *__restrict__ 
 #pragma unroll
     for (int m = 0; m < nf; ++m) {
         const int64_t qa = o + m * nf + j, qb = o + i * nf + m;
-        s += tab.D[m * kMaxNF + i] * ((Ax[qa] + ax) * gbx[qa] + (Cx[qa] + cx) * gby[qa]);
-        s += tab.D[m * kMaxNF + j] * ((Ae[qb] + ae) * gbx[qb] + (Ce[qb] + ce) * gby[qb]);
+        s += tab.D[m * nf + i] * ((Ax[qa] + ax) * gbx[qa] + (Cx[qa] + cx) * gby[qa]);
+        s += tab.D[m * nf + j] * ((Ae[qb] + ae) * gbx[qb] + (Ce[qb] + ce) * gby[qb]);
     }
     gb[q] = s;
 }

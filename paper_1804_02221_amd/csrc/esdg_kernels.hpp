@@ -149,13 +149,14 @@ constexpr int kNumFlags = 8;
 
 // Tile of workgroup b when B = round_up(ntiles, 8) workgroups are launched:
 // hardware places workgroup b on XCD b % 8, so XCD x gets tiles
-// [x*per, (x+1)*per).  Tiles >= ntiles return -1.
+// [x*per, (x+1)*per).  Tiles >= ntiles return -1.  (A tile holds at least one
+// of the at most INT32_MAX elements.)
 __device__ inline int64_t xcd_tile(int64_t ntiles)
 {
-    const int64_t b = blockIdx.x;
-    const int64_t per = (ntiles + kXcds - 1) / kXcds;
-    const int64_t tile = (b % kXcds) * per + b / kXcds;
-    return tile < ntiles ? tile : -1;
+    const uint32_t b = blockIdx.x, n = (uint32_t)ntiles;
+    const uint32_t per = (n + kXcds - 1) / kXcds;
+    const uint32_t tile = (b % kXcds) * per + b / kXcds;
+    return tile < n ? (int64_t)tile : -1;
 }
 
 // Face node k of local side s -> local (i, j).
@@ -172,9 +173,9 @@ __device__ __forceinline__ void side_node(int s, int k, int &i, int &j)
 // Operator tables of one degree, in device memory.
 template <typename R>
 struct Tab {
-    R D[kMaxNF * kMaxNF];     // derivative matrix, row-major
-    R Dz[kMaxNF * kMaxNF];    // the same with a zero diagonal (flux differencing), rows of N + 1
-    R Vinv[kMaxNF * kMaxNF];  // Vandermonde inverse, rows of N + 1
+    R D[kMaxNF * kMaxNF];     // derivative matrix (this and the next two in rows of N + 1)
+    R Dz[kMaxNF * kMaxNF];    // the same with a zero diagonal (flux differencing)
+    R Vinv[kMaxNF * kMaxNF];  // Vandermonde inverse
     R w[kMaxNF];              // LGL weights
     R iw0;                    // 1 / w_0 (end weight)
 };
@@ -294,6 +295,45 @@ __device__ __forceinline__ float rcp_nr(float x)
     return fmaf(r, fmaf(-x, r, 1.0f), r);
 }
 
+// sqrt(x) for x >= 0 from the hardware's reciprocal square root: one coupled
+// Newton step for sqrt(x) and 1/(2 sqrt(x)), then two residual corrections of
+// the root (published as Goldschmidt's iteration).  The library's sqrt scales
+// its argument around the same steps for the sake of subnormal x; here x is a
+// squared wave speed or length.
+__device__ __forceinline__ double sqrt_nr(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    double s = x * y, k = 0.5 * y;
+    const double r = fma(-k, s, 0.5);
+    s = fma(s, r, s);
+    k = fma(k, r, k);
+    s = fma(fma(-s, s, x), k, s);
+    s = fma(fma(-s, s, x), k, s);
+    return x > 0.0 ? s : 0.0;
+}
+__device__ __forceinline__ float sqrt_nr(float x) { return sqrtf(x); }
+
+// s = sqrt(x) and i = 1/sqrt(x) for a positive normal x, the reciprocal with
+// the last Newton step of rcp_nr.
+__device__ __forceinline__ void sqrt_rcp(double x, double &s, double &i)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    double k = 0.5 * y;
+    s = x * y;
+    const double r = fma(-k, s, 0.5);
+    s = fma(s, r, s);
+    k = fma(k, r, k);
+    s = fma(fma(-s, s, x), k, s);
+    s = fma(fma(-s, s, x), k, s);
+    k += k;
+    i = fma(k, fma(-s, k, 1.0), k);
+}
+__device__ __forceinline__ void sqrt_rcp(float x, float &s, float &i)
+{
+    s = sqrtf(x);
+    i = rcp_nr(s);
+}
+
 template <typename R>
 __device__ __forceinline__ R rcp_wet(R h, R h_tol)
 {
@@ -331,8 +371,8 @@ __device__ __forceinline__ void interface_flux(R hm, R um, R vm, R bm, R hp, R u
     const R g = P.g;
     const R utm = nx * um + ny * vm, vtm = nx * vm - ny * um;
     const R utp = nx * up + ny * vp, vtp = nx * vp - ny * up;
-    const R cm = sqrt(g * fmax(hm, R(0)));
-    const R cp = sqrt(g * fmax(hp, R(0)));
+    const R cm = sqrt_nr(g * fmax(hm, R(0)));
+    const R cp = sqrt_nr(g * fmax(hp, R(0)));
     const R ah = R(0.5) * (hm + hp), au = R(0.5) * (utm + utp), av = R(0.5) * (vtm + vtp);
     const R ah2 = R(0.5) * (hm * hm + hp * hp), ac = R(0.5) * (cm + cp);
     R f0 = ah * au;
@@ -381,8 +421,8 @@ __device__ __forceinline__ void interface_flux_delta(R hm, R um, R vm, R bm, R h
     R f1 = au * f0 + R(0.5) * (dut * fo + g * dh * ah);
     R f2 = av * f0 + R(0.5) * dvt * fo;
     if (!P.ec) {
-        const R cm = sqrt(g * fmax(hm, R(0)));
-        const R cp = sqrt(g * fmax(hp, R(0)));
+        const R cm = sqrt_nr(g * fmax(hm, R(0)));
+        const R cp = sqrt_nr(g * fmax(hp, R(0)));
         const R ac = R(0.5) * (cm + cp);
         const R dq1 = g * (dh + (bp - bm)) - R(0.5) * (du * (up + um) + dv * (vp + vm));
         const R dq2 = dut, dq3 = dvt;
@@ -420,10 +460,10 @@ __global__ void geometry_kernel(int64_t K, const double *__restrict__ x, const d
     double xxi = 0, xeta = 0, yxi = 0, yeta = 0;
 #pragma unroll
     for (int m = 0; m < nf; ++m) {
-        xxi += tab.D[i * kMaxNF + m] * (xe[m * nf + j] - x0);
-        yxi += tab.D[i * kMaxNF + m] * (ye[m * nf + j] - y0);
-        xeta += tab.D[j * kMaxNF + m] * (xe[i * nf + m] - x0);
-        yeta += tab.D[j * kMaxNF + m] * (ye[i * nf + m] - y0);
+        xxi += tab.D[i * nf + m] * (xe[m * nf + j] - x0);
+        yxi += tab.D[i * nf + m] * (ye[m * nf + j] - y0);
+        xeta += tab.D[j * nf + m] * (xe[i * nf + m] - x0);
+        yeta += tab.D[j * nf + m] * (ye[i * nf + m] - y0);
     }
     const double J = xxi * yeta - xeta * yxi;
     if (!(J > 0.0)) atomicOr(bad, 1);
@@ -440,10 +480,10 @@ __global__ void geometry_kernel(int64_t K, const double *__restrict__ x, const d
         double cxxi = 0, cxeta = 0, cyxi = 0, cyeta = 0;
 #pragma unroll
         for (int m = 0; m < nf; ++m) {
-            cxxi += tab.D[c * kMaxNF + m] * (xe[m * nf + c] - x0);
-            cyxi += tab.D[c * kMaxNF + m] * (ye[m * nf + c] - y0);
-            cxeta += tab.D[c * kMaxNF + m] * (xe[c * nf + m] - x0);
-            cyeta += tab.D[c * kMaxNF + m] * (ye[c * nf + m] - y0);
+            cxxi += tab.D[c * nf + m] * (xe[m * nf + c] - x0);
+            cyxi += tab.D[c * nf + m] * (ye[m * nf + c] - y0);
+            cxeta += tab.D[c * nf + m] * (xe[c * nf + m] - x0);
+            cyeta += tab.D[c * nf + m] * (ye[c * nf + m] - y0);
         }
         const R r0 = (R)cyeta, r1 = (R)(-cxeta), r2 = (R)(-cyxi), r3 = (R)cxxi;
         if (p == 0) {
@@ -482,16 +522,16 @@ __global__ void bathymetry_kernel(int64_t K, const double *__restrict__ x, const
     auto met = [&](int a, int c, double &xxi, double &xeta, double &yxi, double &yeta) {
         xxi = xeta = yxi = yeta = 0.0;
         for (int m = 0; m < nf; ++m) {
-            xxi += tab.D[a * kMaxNF + m] * (xe[m * nf + c] - x0);
-            yxi += tab.D[a * kMaxNF + m] * (ye[m * nf + c] - y0);
-            xeta += tab.D[c * kMaxNF + m] * (xe[a * nf + m] - x0);
-            yeta += tab.D[c * kMaxNF + m] * (ye[a * nf + m] - y0);
+            xxi += tab.D[a * nf + m] * (xe[m * nf + c] - x0);
+            yxi += tab.D[a * nf + m] * (ye[m * nf + c] - y0);
+            xeta += tab.D[c * nf + m] * (xe[a * nf + m] - x0);
+            yeta += tab.D[c * nf + m] * (ye[a * nf + m] - y0);
         }
     };
     double Db_xi = 0, Dyb_xi = 0, Dxb_xi = 0, Db_eta = 0, Dyb_eta = 0, Dxb_eta = 0;
     for (int m = 0; m < nf; ++m) {
         double a0, a1, a2, a3;
-        const double dxi = tab.D[i * kMaxNF + m], deta = tab.D[j * kMaxNF + m];
+        const double dxi = tab.D[i * nf + m], deta = tab.D[j * nf + m];
         met(m, j, a0, a1, a2, a3);   // node (m, j)
         const double bm = be[m * nf + j];
         Db_xi += dxi * bm;
@@ -888,7 +928,7 @@ __device__ __forceinline__ void viscous_flux_at(int i, int j, const R *su, const
     const R ou = kJumpForm<R> ? u0 : R(0), ov = kJumpForm<R> ? v0 : R(0);
 #pragma unroll
     for (int m = 0; m < nf; ++m) {
-        const R di = tab.D[i * kMaxNF + m], dj = tab.D[j * kMaxNF + m];
+        const R di = tab.D[i * nf + m], dj = tab.D[j * nf + m];
         dxu += di * (su[m * nf + j] - ou);
         dxv += di * (sv[m * nf + j] - ov);
         deu += dj * (su[i * nf + m] - ou);
@@ -1114,7 +1154,7 @@ __global__ __launch_bounds__(Shape<N>::T) void av_div_kernel(ListArgs<N, R> a)
             const R o2 = kJumpForm<R> ? s_Fv[2][t] : R(0), o3 = kJumpForm<R> ? s_Fv[3][t] : R(0);
 #pragma unroll
             for (int mm = 0; mm < nf; ++mm) {
-                const R di = a.tg->D[i * kMaxNF + mm], dj = a.tg->D[j * kMaxNF + mm];
+                const R di = a.tg->D[i * nf + mm], dj = a.tg->D[j * nf + mm];
                 Lv2 += di * (s_Fv[0][base + mm * nf + j] - o0) + dj * (s_Fv[2][base + i * nf + mm] - o2);
                 Lv3 += di * (s_Fv[1][base + mm * nf + j] - o1) + dj * (s_Fv[3][base + i * nf + mm] - o3);
             }
@@ -1149,9 +1189,9 @@ __device__ __forceinline__ R cfl_bound(R h, R hu, R hv, R Ax, R Cx, R Ae, R Ce, 
 {
     const R ih = rcp_wet(h, P.h_tol);
     const R u = hu * ih, v = hv * ih;
-    const R cs = sqrt(P.g * fmax(h, R(0)));
-    const R lx = fabs(Ax * u + Cx * v) + cs * sqrt(Ax * Ax + Cx * Cx);
-    const R le = fabs(Ae * u + Ce * v) + cs * sqrt(Ae * Ae + Ce * Ce);
+    const R cs = sqrt_nr(P.g * fmax(h, R(0)));
+    const R lx = fabs(Ax * u + Cx * v) + cs * sqrt_nr(Ax * Ax + Cx * Cx);
+    const R le = fabs(Ae * u + Ce * v) + cs * sqrt_nr(Ae * Ae + Ce * Ce);
     return lx + le > R(0) ? P.cfl * (R(2) / R(N + 1)) * J / (lx + le) : R(3.0e38);
 }
 
@@ -1199,41 +1239,44 @@ struct StageArgs {
 };
 
 // Face slot data loaded ahead of the LDS staging (slots t, t + T, ... of lane t).
-// Kept small (it is live across the LDS staging): the neighbour element as
-// int32 and one packed word, the neighbour node's index recomputed from them.
+// Kept small (it is live across the LDS staging): the neighbour element and
+// one packed word.
 template <typename R>
 struct FacePrefetch {
     int32_t en = 0;          // neighbour element
-    int code = 0;            // neighbour side | face node << 2 | (visc_nbr) << 8
+    int code = 0;            // neighbour side | face node << 2 | (visc_nbr) << 8 | wall << 9
     R h = 0, hu = 0, hv = 0, bo = 0, bn = 0;
     __device__ int ns() const { return code & 3; }
     __device__ int kk() const { return (code >> 2) & 63; }
     // with AV: the element has no viscosity, its neighbour has
     __device__ bool visc_nbr() const { return (code >> 8) & 1; }
+    __device__ bool wall() const { return (code >> 9) & 1; }
 };
 
+// Slot f of the tile whose first element is e0.
 template <int N, typename R, int E, int NF>
-__device__ __forceinline__ void prefetch_face(const StageArgs<R> &a, int t, int64_t e0, FacePrefetch<R> &pf)
+__device__ __forceinline__ void prefetch_face(const StageArgs<R> &a, int f, int64_t e0, FacePrefetch<R> &pf)
 {
     constexpr int nf = N + 1, np = nf * nf;
-    if (t >= NF) return;
-    const int fel = t / (4 * nf), s = (t / nf) & 3, k = t - (t / nf) * nf;
-    const int64_t fe = e0 + fel;
-    if (fe >= a.m.K) return;
-    int64_t en;
-    int ns, kk;
-    const int64_t qn = nbr_node<N>(a.m, fe, s, k, en, ns, kk);
-    const int64_t ql = qn - e0 * np;
-    if (!(ql >= 0 && ql < E * np)) {
+    if (f >= NF) return;
+    const int side = f / nf, fel = side / 4, k = f - side * nf;
+    if (e0 + fel >= a.m.K) return;
+    const int32_t en = (a.m.nbr + 4 * e0)[side];
+    const int c = (a.m.code + 4 * e0)[side];
+    pf.bo = (a.m.bface + e0 * 4 * nf)[f];
+    const int ns = c & 3, kk = (c & 4) ? N - k : k;
+    int i, j;
+    side_node<N>(ns, kk, i, j);
+    if ((uint32_t)(en - (int32_t)e0) >= (uint32_t)E) {
+        const uint64_t qn = (uint64_t)(uint32_t)en * np + (uint32_t)(i * nf + j);
         pf.h = a.h[qn];
         pf.hu = a.hu[qn];
         pf.hv = a.hv[qn];
     }
-    pf.bo = a.m.bface[(fe * 4 + s) * nf + k];
-    pf.bn = a.m.bface[(en * 4 + ns) * nf + kk];
-    const bool vn = a.eps && !(a.eps[fe] > R(0)) && a.eps[en] > R(0);
-    pf.en = (int32_t)en;
-    pf.code = ns | (kk << 2) | ((int)vn << 8);
+    pf.bn = a.m.bface[(uint64_t)(uint32_t)en * (4 * nf) + (uint32_t)(ns * nf + kk)];
+    const bool vn = a.eps && !((a.eps + e0)[fel] > R(0)) && a.eps[en] > R(0);
+    pf.en = en;
+    pf.code = ns | (kk << 2) | ((int)vn << 8) | ((c & 8) << 6);
 }
 
 template <int N, typename R, int MODE, int V>
@@ -1274,19 +1317,26 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
     // a retry of some instances: tiles with none of their elements leave
     // every output as it is
     if (a.imask && !block_any<T>(act)) return;
-    const int64_t q = e * np + p;
+    // Node el*np + p of the tile is lane t's: every field is read and written
+    // at its tile's start (a scalar) plus the one lane offset, which lanes
+    // without a node of their own set to the tile's first node (their values
+    // are never stored or summed).
+    const int64_t q0 = e0 * np;
+    const uint32_t tq = act ? (uint32_t)t : 0u;
     const Phys<R> &P = a.P;
     const bool av = a.eps != nullptr;
 
-    R h = 0, hu = 0, hv = 0, Ax = 0, Cx = 0, Ae = 0, Ce = 0;
+    // the table first: its staging then waits for nothing behind it
+    static_assert(nf * nf <= T, "one table entry per lane");
+    const R dz_t = a.tg->Dz[t < nf * nf ? t : 0];
+    const R h = (a.h + q0)[tq], hu = (a.hu + q0)[tq], hv = (a.hv + q0)[tq];
+    R Ax = 0, Cx = 0, Ae = 0, Ce = 0;
     double xr = 0, yr = 0;
-    if (act) {
-        h = a.h[q]; hu = a.hu[q]; hv = a.hv[q];
-        if constexpr (kMetricInKernel<N, R>) {
-            xr = a.m.xr[q]; yr = a.m.yr[q];
-        } else {
-            Ax = a.m.Ax[q]; Cx = a.m.Cx[q]; Ae = a.m.Ae[q]; Ce = a.m.Ce[q];
-        }
+    if constexpr (kMetricInKernel<N, R>) {
+        xr = (a.m.xr + q0)[tq]; yr = (a.m.yr + q0)[tq];
+    } else {
+        Ax = (a.m.Ax + q0)[tq]; Cx = (a.m.Cx + q0)[tq];
+        Ae = (a.m.Ae + q0)[tq]; Ce = (a.m.Ce + q0)[tq];
     }
     // single precision: the stored terms are relative to the element's
     // middle node (kMetricRel); staged and held as they are until the volume
@@ -1323,7 +1373,7 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
         static_assert(3 * NF >= nf * nf, "D in the face-flux slots");
         R *const s_D = &s_fl[0][0];
         s_a[st] = V2{xr, yr};
-        for (int c = t; c < nf * nf; c += T) s_D[c] = a.tg->D[(c / nf) * kMaxNF + (c - (c / nf) * nf)];
+        for (int c = t; c < nf * nf; c += T) s_D[c] = a.tg->D[c];
         lds_sync<T>();
         const int base = el * PS;
         R xxi = 0, yxi = 0, xeta = 0, yeta = 0;
@@ -1343,26 +1393,19 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
     s_b[st] = V2{Ae, Ce};
     // the per-lane table entries of the volume term from LDS rather than
     // through the vector memory path (3-6% faster)
-    static_assert(nf * nf <= T, "one table entry per lane");
-    if (t < nf * nf) s_dz[t] = a.tg->Dz[t];
+    if (t < nf * nf) s_dz[t] = dz_t;
     lds_sync<T>();
 
     // ---- interface: (1/w_0) J^surf F*(own, nbr, n_out) per face node; for
     // an element without viscosity next to one with viscosity, also its only
     // viscous term: (1/(2 w_0)) n_s . Fv_nbr (its own viscous fluxes are 0) ----
     auto face_slot = [&](const int f, const FacePrefetch<R> &pfr) {
-        const int fel = f / (4 * nf), s = (f / nf) & 3, k = f - (f / nf) * nf;
-        const int64_t fe = e0 + fel;
+        const int side = f / nf, fel = side / 4, s = side & 3, k = f - side * nf;
         R c0 = 0, c1 = 0, c2 = 0;
-        if (fe < a.m.K) {
+        if (e0 + fel < a.m.K) {
             int fi, fj;
             side_node<N>(s, k, fi, fj);
             const int lp = fel * PS + fi * RS + stage_col<N, V>(fi, fj);
-            const int64_t en = pfr.en;
-            const int ns = pfr.ns(), kk = pfr.kk();
-            int ni, nj;
-            side_node<N>(ns, kk, ni, nj);
-            const int64_t qn = en * np + ni * nf + nj;
             // outward scaled normal: +-J grad(xi) on xi = +-1, +-J grad(eta) on eta = +-1
             V2 dir = (s & 1) ? s_a[lp] : s_b[lp];
             if constexpr (kMetricRel<R>) {
@@ -1371,14 +1414,15 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
             }
             const R sg = (s == 0 || s == 3) ? R(-1) : R(1);
             const R snx = sg * dir.x, sny = sg * dir.y;
-            const R js = sqrt(snx * snx + sny * sny);
-            const R ijs = rcp_nr(js);
+            R js, ijs;
+            sqrt_rcp(snx * snx + sny * sny, js, ijs);
             // neighbour trace: from LDS when the neighbour is in this workgroup
-            const int64_t ql = qn - e0 * np;
-            R hn, un, vn, bo, bn;
-            if (ql >= 0 && ql < E * np) {
-                const int qe = (int)ql / np, qp = (int)ql - qe * np;
-                const int qs = qe * PS + (qp / nf) * RS + stage_col<N, V>(qp / nf, qp - (qp / nf) * nf);
+            const uint32_t enl = (uint32_t)(pfr.en - (int32_t)e0);
+            R hn, un, vn;
+            if (enl < (uint32_t)E) {
+                int ni, nj;
+                side_node<N>(pfr.ns(), pfr.kk(), ni, nj);
+                const int qs = (int)enl * PS + ni * RS + stage_col<N, V>(ni, nj);
                 hn = s_h[qs];
                 const V2 w = s_w[qs];
                 un = w.x;
@@ -1389,9 +1433,8 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
                 un = pfr.hu * in;
                 vn = pfr.hv * in;
             }
-            bo = pfr.bo;
-            bn = pfr.bn;
-            if (is_wall(a.m, fe, s)) wall_mirror(snx * ijs, sny * ijs, un, vn);
+            const R bo = pfr.bo, bn = pfr.bn;
+            if (pfr.wall()) wall_mirror(snx * ijs, sny * ijs, un, vn);
             R F0, F1, F2;
             const V2 wl = s_w[lp];
             if constexpr (kJumpForm<R>)
@@ -1408,7 +1451,7 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
             const R pen = R(0.25) * P.g * a.tab.iw0 * (s_h[lp] + hn) * (bn - bo);
             c1 += pen * snx; c2 += pen * sny;
             if (av && pfr.visc_nbr()) {
-                const R *vn = a.vtr + ((en * 4 + ns) * nf + kk) * 4;
+                const R *vn = a.vtr + (((int64_t)pfr.en * 4 + pfr.ns()) * nf + pfr.kk()) * 4;
                 const R hw = R(0.5) * a.tab.iw0;
                 c1 -= hw * (snx * vn[0] + sny * vn[2]);
                 c2 -= hw * (snx * vn[1] + sny * vn[3]);
@@ -1549,11 +1592,9 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
     // cost a 128^2 mesh at N = 7 3%)
     const StageArgs<R> &late = kernarg<StageArgs<R>>();
     const Phys<R> &PL = late.P;
-    R bxv = 0, byv = 0, Lv2 = 0, Lv3 = 0;
-    if (act) {
-        bxv = late.m.bx[q]; byv = late.m.by[q];
-        if (av && eps_e > R(0)) { Lv2 = late.lv2[q]; Lv3 = late.lv3[q]; }
-    }
+    const R bxv = (late.m.bx + q0)[tq], byv = (late.m.by + q0)[tq];
+    R Lv2 = 0, Lv3 = 0;
+    if (av && eps_e > R(0)) { Lv2 = (late.lv2 + q0)[tq]; Lv3 = (late.lv3 + q0)[tq]; }
     const R iJ = act ? rcp_nr(J) : R(0);
     const R hg = R(0.5) * PL.g * h;
     const R R1 = -L1 * iJ;
@@ -1561,7 +1602,7 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
     const R R3 = (-L3 - hg * byv + Lv3) * iJ;
 
     if constexpr (MODE == kModeRhs) {
-        if (act) { late.oh[q] = R1; late.ohu[q] = R2; late.ohv[q] = R3; }
+        if (act) { (late.oh + q0)[tq] = R1; (late.ohu + q0)[tq] = R2; (late.ohv + q0)[tq] = R3; }
         return;
     } else {
         const R dt = (R)late.dt[late.inst ? 8 * (int64_t)late.inst[act ? e : e0] : 0];
@@ -1569,14 +1610,13 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
         R d0 = 0, d1 = 0, d2 = 0;
         if constexpr (MODE == kModeLsrk) {
             // the first stage has a_1 = 0: the register is not read
-            if (act && late.ca != R(0)) { d0 = late.dh[q]; d1 = late.dhu[q]; d2 = late.dhv[q]; }
+            if (late.ca != R(0)) { d0 = (late.dh + q0)[tq]; d1 = (late.dhu + q0)[tq]; d2 = (late.dhv + q0)[tq]; }
             d0 = late.ca * d0 + dt * R1;
             d1 = late.ca * d1 + dt * R2;
             d2 = late.ca * d2 + dt * R3;
             nh = h + late.cb * d0; nhu = hu + late.cb * d1; nhv = hv + late.cb * d2;
         } else {
-            R w0 = 0, w1 = 0, w2 = 0;
-            if (act) { w0 = late.h0[q]; w1 = late.hu0[q]; w2 = late.hv0[q]; }
+            const R w0 = (late.h0 + q0)[tq], w1 = (late.hu0 + q0)[tq], w2 = (late.hv0 + q0)[tq];
             nh = late.ca * w0 + late.cb * (h + dt * R1);
             nhu = late.ca * w1 + late.cb * (hu + dt * R2);
             nhv = late.ca * w2 + late.cb * (hv + dt * R3);
@@ -1620,9 +1660,9 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
         // their sum non-finite) is reported once per esdg_step
         if (act && !__builtin_isfinite(nh + nhu + nhv)) atomicOr(&late.flags[kFlagNonFinite], 1);
         if (act) {
-            late.oh[q] = nh; late.ohu[q] = nhu; late.ohv[q] = nhv;
+            (late.oh + q0)[tq] = nh; (late.ohu + q0)[tq] = nhu; (late.ohv + q0)[tq] = nhv;
             if constexpr (MODE == kModeLsrk) {
-                if (late.store_du) { late.dh[q] = d0; late.dhu[q] = d1; late.dhv[q] = d2; }
+                if (late.store_du) { (late.dh + q0)[tq] = d0; (late.dhu + q0)[tq] = d1; (late.dhv + q0)[tq] = d2; }
             }
         }
         R en = R(0);

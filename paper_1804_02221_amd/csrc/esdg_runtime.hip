@@ -981,9 +981,9 @@ int upload_mesh_impl(esdg_ctx *ctx, int N, int64_t K, const double *x, const dou
         ctx->td.w[i] = (double)ctx->ht.w[i];
         ctx->tf.w[i] = (float)ctx->ht.w[i];
         for (int j = 0; j <= N; ++j) {
-            ctx->td.D[i * kMaxNF + j] = (double)ctx->ht.D[i][j];
-            ctx->tf.D[i * kMaxNF + j] = (float)ctx->ht.D[i][j];
             const int c = i * (N + 1) + j;
+            ctx->td.D[c] = (double)ctx->ht.D[i][j];
+            ctx->tf.D[c] = (float)ctx->ht.D[i][j];
             ctx->td.Dz[c] = i == j ? 0.0 : (double)ctx->ht.D[i][j];
             ctx->tf.Dz[c] = i == j ? 0.0f : (float)ctx->ht.D[i][j];
             ctx->td.Vinv[c] = (double)ctx->ht.Vinv[i][j];
