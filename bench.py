@@ -61,8 +61,8 @@ def stage_bytes(N: int, K: int, av: bool, real_bytes: int, stage_index: int, n_v
     in FP32 also 4/element, geometry_elem_fields), split bathymetry
     derivatives (2/node), face
     bathymetry (4(N+1)/element); with AV the element viscosity (1/element)
-    and, for the n_visc elements with viscosity, their viscous face fluxes
-    (16(N+1)/element, read by their neighbours) and viscous terms (2/node).
+    and, for n_visc elements with viscosity, the viscous face fluxes (16(N+1))
+    and terms (2/node) of a kernel that reads them from passes of their own.
     Writes: W (3/node), dU (3/node, not on the last stage: the next step's
     first stage does not read it); on the last stage with the limiter the
     face records of the new state for the next time-step pass (h, u, v at the
@@ -89,26 +89,6 @@ def rhs_bytes(N: int, K: int, av: bool, real_bytes: int, n_visc: int = 0) -> flo
     visc = (16 * nf + 2 * np_) * n_visc if av else 0
     return ((3 + geometry_fields(N, real_bytes) + 2 + 3) * K * np_
             + (4 * nf + geometry_elem_fields(real_bytes) + (1 if av else 0)) * K + visc) * real_bytes
-
-
-def av_faces_bytes(N: int, n_visc: int, real_bytes: int) -> float:
-    """Algorithmic bytes of the BR1 face-flux pass over n_visc viscous
-    elements: per element it reads W (3 (N+1)^2), the neighbours' traces at
-    its 4(N+1) face nodes (3 each), the metric directions at its face nodes
-    (4 each), its viscosity and face map (4 x (4 + 1) bytes); it writes the
-    four viscous flux components at its face nodes (16 (N+1))."""
-    nf = N + 1
-    return n_visc * ((3 * nf * nf + 12 * nf + 16 * nf + 1 + 16 * nf) * real_bytes + 20)
-
-
-def av_div_bytes(N: int, n_visc: int, real_bytes: int) -> float:
-    """Algorithmic bytes of the viscous-divergence pass: per viscous element
-    W (3 (N+1)^2), neighbour traces (12 (N+1)), metric directions
-    (4 (N+1)^2), its own and its neighbours' viscosity (5), the neighbours'
-    face fluxes (16 (N+1)), the face map; writes L^v (2 (N+1)^2)."""
-    nf = N + 1
-    np_ = nf * nf
-    return n_visc * ((3 * np_ + 12 * nf + 4 * np_ + 5 + 16 * nf + 2 * np_) * real_bytes + 20)
 
 
 def dt_pass_bytes(N: int, K: int, av: bool, real_bytes: int) -> float:
@@ -476,8 +456,8 @@ def dam_break_bench(esdg, dev, stream, steps: int, warmup: int):
     """The curvilinear wet/dry dam break (128x128 elements, N=7, AV with
     eps0=0.025, limiter, LSRK(5,4), adaptive step): the hot path with its
     non-smooth parts active.  Reports the stage kernel (bytes including the
-    viscous elements' terms), the two viscosity passes and the time-step
-    pass against the HBM peak, the viscous and limited counts."""
+    viscous elements' face fluxes) and the time-step pass against the HBM
+    peak, the viscous and limited counts."""
     import torch
     from paper_1804_02221_amd.inputs import dam_break
     w = dam_break(128, 7)
@@ -511,7 +491,8 @@ def dam_break_bench(esdg, dev, stream, steps: int, warmup: int):
     s.close()
     n_visc = 0.5 * (v0 + v1)
     st_ms, st_n = prof["stage"]
-    stage_b = sum(stage_bytes(N, K, True, 8, k, int(round(n_visc))) for k in range(5)) / 5
+    # per viscous element its face fluxes' own part (8(N+1)): written by the stage before, read by neighbours
+    stage_b = sum(stage_bytes(N, K, True, 8, k) for k in range(5)) / 5 + n_visc * 16 * (N + 1) * 8
     res = dict(workload=("curvilinear wet/dry dam break, 128x128 elements of [0,10]^2, N=7, 8-Gaussian bottom, "
                          "AV eps0=0.025 + limiter, ES flux, LSRK(5,4), adaptive dt (CFL, viscous, Lemma 2)"),
                nodes=nodes, steps=steps, warmup=warmup, t_sim=t_sim, min_h=d[5],
@@ -525,13 +506,6 @@ def dam_break_bench(esdg, dev, stream, steps: int, warmup: int):
         t = st_ms / st_n * 1e-3
         rl["stage_kernel"] = {"bytes_per_launch": stage_b, "GBs": stage_b / t / 1e9,
                               "frac": stage_b / t / 1e9 / HBM_PEAK_GBS}
-    for k, fn in (("av_faces", av_faces_bytes), ("av_div", av_div_bytes)):
-        ms, n = prof[k]
-        if n:
-            b = fn(N, n_visc, 8)
-            rl[k + "_kernel"] = {"bytes_per_launch": b, "GBs": b / (ms / n * 1e-3) / 1e9,
-                                 "frac": b / (ms / n * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                                 "note": "bytes of the listed viscous elements only (mean count)"}
     ms, n = prof["dt"]
     if n:
         b = dt_pass_bytes(N, K, True, 8)
@@ -664,7 +638,7 @@ def main():
         d = s.diagnostics()
         log(f"N={N} FP{precision}: {steps} steps in {el:.3f} s, t={t_sim:.4g}, min h={d[5]:.3g}, "
             f"stage variant {choice}")
-        per_step = sum(stage_bytes(N, K, av, rb, k, n_visc) for k in range(5))
+        per_step = sum(stage_bytes(N, K, av, rb, k) for k in range(5))
         st_ms, st_n = prof["stage"]
         stage_mean_ms = st_ms / max(st_n, 1)
         achieved = per_step * steps / (st_ms * 1e-3) / 1e9

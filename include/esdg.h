@@ -265,9 +265,9 @@ int esdg_profile_read(esdg_ctx *ctx, double *stage_ms, int64_t *stage_launches,
 int esdg_profile_read_adjoint(esdg_ctx *ctx, double *ms, int64_t *launches);
 /* Per kernel class, summed event milliseconds ms[k] and launches[k] since
  * the last read (all classes then reset): k = 0 stage kernel, 1 indicator
- * (viscosity of a state no stage produced), 2 viscous face fluxes (BR1,
- * Theorem 1), 3 viscous divergence (eq. ViscTermsDisc), 4 time-step pass
- * (eq. CFLConstraints and the CFL/viscous bounds), 5 adjoint reverse stage.
+ * (viscosity of a state no stage produced), 2 and 3 none (the viscous terms
+ * are part of the stage kernel), 4 time-step pass (eq. CFLConstraints and the
+ * CFL/viscous bounds), 5 adjoint reverse stage.
  * esdg_profile_read's av figures are classes 1-3. */
 int esdg_profile_read_kernels(esdg_ctx *ctx, double ms[6], int64_t launches[6]);
 
@@ -278,7 +278,7 @@ int esdg_profile_read_kernels(esdg_ctx *ctx, double ms[6], int64_t launches[6]);
  * elements fill it -- N = 2, 3, 7 -- else 256 threads) with its register
  * budget and partner-loop unroll; 1 the alternative workgroup size (256
  * resp. 128 threads); 2 the default tile with one wave per SIMD less in its
- * register budget; 3 the default tile with the other partner-loop unroll;
+ * register budget; 3 the default tile with a smaller partner-loop unroll;
  * 4 the default tile with bank-conflict-free staging rows: padded by one
  * node (the paper's LDS padding, more LDS per tile), at N = 7 XOR-swizzled
  * columns instead (no more LDS).

@@ -109,55 +109,14 @@ hipError_t Launch<N, R>::indicator(const Bufs &B, int buf, const Phys<R> &P, con
     a.tab = uniform_entries(t, N);
     a.tg = (const Tab<R> *)B.tabg;
     a.K = B.K;
+    a.m = mesh_view<R>(B);
     a.h = (const R *)B.W[buf][0];
+    a.hu = (const R *)B.W[buf][1];
+    a.hv = (const R *)B.W[buf][2];
     a.eps = (R *)B.eps[buf];
-    a.list = B.list[buf];
-    a.count = B.count + buf;
+    a.vfl = (R *)B.vfl[buf];
     a.ntiles = ntiles_of<N>(B.K);
     launch_ev(indicator_kernel<N, R>, tile_grid<N>(B.K), dim3(Shape<N>::T), s, ev, a);
-    return hipGetLastError();
-}
-
-template <int N, typename R>
-static ListArgs<N, R> list_args(const Bufs &B, int in, const Phys<R> &P, const Tab<R> &t)
-{
-    ListArgs<N, R> a;
-    a.m = mesh_view<R>(B);
-    a.P = P;
-    a.tab = uniform_entries(t, N);
-    a.tg = (const Tab<R> *)B.tabg;
-    a.h = (const R *)B.W[in][0];
-    a.hu = (const R *)B.W[in][1];
-    a.hv = (const R *)B.W[in][2];
-    a.eps = (const R *)B.eps[in];
-    a.list = B.list[in];
-    a.count = B.count + in;
-    a.vtr = (R *)B.vtr;
-    a.lv2 = (R *)B.lv[0];
-    a.lv3 = (R *)B.lv[1];
-    a.count_reset = nullptr;
-    return a;
-}
-
-// Fixed grid for the list passes: a few workgroups per CU, grid-stride over
-// the list (its length is only known on the device).
-constexpr unsigned kListBlocks = 1024;
-
-template <int N, typename R>
-hipError_t Launch<N, R>::av_faces(const Bufs &B, int in, const Phys<R> &P, const Tab<R> &t, hipStream_t s,
-                                  Ev ev)
-{
-    launch_ev(av_faces_kernel<N, R>, dim3(kListBlocks), dim3(Shape<N>::T), s, ev, list_args<N, R>(B, in, P, t));
-    return hipGetLastError();
-}
-
-template <int N, typename R>
-hipError_t Launch<N, R>::av_div(const Bufs &B, int in, int reset, const Phys<R> &P, const Tab<R> &t,
-                                hipStream_t s, Ev ev)
-{
-    ListArgs<N, R> a = list_args<N, R>(B, in, P, t);
-    a.count_reset = reset >= 0 ? B.count + reset : nullptr;
-    launch_ev(av_div_kernel<N, R>, dim3(kListBlocks), dim3(Shape<N>::T), s, ev, a);
     return hipGetLastError();
 }
 
@@ -207,12 +166,9 @@ hipError_t Launch<N, R>::stage(const Bufs &B, const StageCall &c, const Phys<R> 
     a.dhv = (R *)B.dU[2];
     a.store_du = c.store_du ? 1 : 0;
     a.eps = c.av ? (const R *)B.eps[c.in] : nullptr;
-    a.vtr = (const R *)B.vtr;
-    a.lv2 = (const R *)B.lv[0];
-    a.lv3 = (const R *)B.lv[1];
+    a.vfl = (const R *)B.vfl[c.in];
     a.eps_out = c.out_rhs ? nullptr : (R *)B.eps[c.out];
-    a.list_out = c.out_rhs ? nullptr : B.list[c.out];
-    a.count_out = c.out_rhs ? nullptr : B.count + c.out;
+    a.vfl_out = c.out_rhs ? nullptr : (R *)B.vfl[c.out];
     a.dtc_out = c.dt_next && !c.out_rhs ? (R *)B.dtc : nullptr;
     a.dtv_out = c.dt_next && !c.out_rhs && c.av ? (R *)B.dtv : nullptr;
     a.frec_out = c.dt_next && !c.out_rhs && P.limiter_on ? (R *)B.frec : nullptr;

@@ -9,11 +9,10 @@
 // mapping is XCD-aware so that each of the eight XCDs sweeps one contiguous
 // block of tiles and neighbour traces mostly hit its own L2.
 //
-// Kernels (per RK stage): av_kernel (artificial viscosity: element
-// viscosity from the modal indicator and the BR1 viscous fluxes on the
-// element faces, only with AV on), stage_kernel (split-form volume term,
-// interface flux, source, viscous divergence, stage update and positivity
-// limiter, fused); per step: dt_kernel + dt_finalize_kernel.
+// Kernels: per RK stage stage_kernel (split-form volume term, interface flux,
+// source, artificial viscosity, stage update, positivity limiter and the
+// modal indicator of the result, fused); per step dt_kernel +
+// dt_finalize_kernel; indicator_kernel for a state no stage produced.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <cstdint>
@@ -63,19 +62,19 @@ struct TileShape {
 //   0  the default tile of Shape, its register budget and partner unroll;
 //   1  the alternative workgroup size (AltThreads), no register budget;
 //   2  the default tile with one wave per SIMD less in its register budget
-//      (more registers, no spills where the default spills);
-//   3  the default tile with the other partner-loop unroll (full where the
-//      default unrolls partly, by two where it unrolls fully);
+//      (more registers);
+//   3  the default tile with the partner loops unrolled by two instead of
+//      fully;
 //   4  the default tile with bank-conflict-free staging rows: padded by one
 //      node (the paper's LDS padding, appendix C), or at N = 7 XOR-swizzled
-//      columns (no more LDS; StageCfg::SWZ).
+//      columns (no more LDS; StageCfg::SWZ); unrolled by two (a full unroll
+//      of the padded rows spills 50-270 registers).
 // Default register budget in the FP64 update modes: six waves per SIMD at
-// N = 6, five otherwise (N = 7 reaches six by its partner-loop unroll); in
-// the FP32 update modes eight (seven for variant 2, none for variant 1): left
-// free, the compiler gave some FP32 variants 100-120 registers; no
-// constraint in the right-hand-side mode.  Default unroll: fully,
-// except at N = 7 with one-wave tiles (by two: 79 VGPRs and six waves per
-// SIMD instead of five), N = 6 (by two) and N = 8 (by three: five waves).
+// N = 6 and 7, five otherwise; in the FP32 update modes eight (seven for
+// variant 2, none for variant 1): left free, the compiler gave some FP32
+// variants 100-120 registers; no constraint in the right-hand-side mode.
+// Against an unroll by two the full one runs 2-3% faster at N = 6 and within
+// 1% at the other degrees.
 constexpr int kStageVariants = 5;
 
 template <int N, int V>
@@ -84,8 +83,7 @@ struct StageCfg {
     static constexpr int T = V == 1 ? AltThreads<N>::value : Shape<N>::T;
     static constexpr int base_waves = V == 1 ? 1 : ((N == 6 || N == 7) ? 6 : 5);
     static constexpr int waves = V == 2 ? base_waves - 1 : base_waves;
-    static constexpr int vu_default = (N == 7 && T == 64) ? 2 : (N == 8 ? 3 : (N == 6 ? 2 : N + 1));
-    static constexpr int VU = V == 3 ? (vu_default == N + 1 ? 2 : N + 1) : vu_default;
+    static constexpr int VU = V >= 3 ? 2 : N + 1;
     // Variant 4 avoids the LDS bank conflicts of the eta-direction partner
     // reads (a wave reads column mm of every row, rows 16(N+1) bytes apart in
     // FP64: at N = 7 eight rows on two bank groups).  At N = 7 the columns of
@@ -135,6 +133,14 @@ __device__ __forceinline__ const A &kernarg()
     auto p = __builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(p));
     return *(const A *)p;
+}
+
+// x, as a value the compiler cannot know: what is computed from it behind
+// this point is computed there, not kept in registers from further up.
+__device__ __forceinline__ int fresh(int x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
 }
 
 constexpr int kXcds = 8;
@@ -347,6 +353,14 @@ __device__ __forceinline__ R rcp_wet(R h, R h_tol)
 // which double precision absorbs and single precision does not.
 template <typename R>
 constexpr bool kJumpForm = sizeof(R) == 4;
+
+// The stage kernel computes its lanes' places in the tile a second time after
+// the volume sums (fresh) instead of keeping them where registers are short:
+// in double precision (stage of a smooth flow, N = 3: 46.0 -> 40.8 us, N = 4:
+// 56.0 -> 49.5, N = 6: 57.2 -> 55.7, others even), in single precision at N =
+// 5 (36.7 -> 32.8 us; others 1-3% slower).
+template <int N, typename R>
+constexpr bool kFreshLanes = sizeof(R) == 8 || N == 5;
 
 // At N <= 4 the double-precision stage kernel reads each node's two
 // coordinates (relative to its element's first node) instead of its four
@@ -910,273 +924,6 @@ __device__ __forceinline__ void stage_vinv(R *dst, const Tab<R> &tab, int t)
     for (int q = t; q < nf * nf; q += T) dst[q] = tab.Vinv[q];
 }
 
-// Viscous physical fluxes at node (i,j) of the element whose u, v are in
-// LDS (su, sv offset to the element), with U*, V* per face slot in us, vs
-// (BR1 gradients of eq. BR1 with the lifted reference derivatives).
-template <int N, typename R>
-__device__ __forceinline__ void viscous_flux_at(int i, int j, const R *su, const R *sv, const R *us,
-                                                const R *vs, R Ax, R Cx, R Ae, R Ce, R he,
-                                                const Tab<R> &tab, R &Fv2, R &Fv3, R &Gv2, R &Gv3)
-{
-    constexpr int nf = N + 1;
-    const R u0 = su[i * nf + j], v0 = sv[i * nf + j];
-    R dxu = 0, dxv = 0, deu = 0, dev = 0;
-    // single precision: the sums over the jumps from the node's own values
-    // (D's rows sum to zero), so that neither the rounding of the table's
-    // row sums nor that of products at the size of the values themselves
-    // enters the derivatives (kJumpForm)
-    const R ou = kJumpForm<R> ? u0 : R(0), ov = kJumpForm<R> ? v0 : R(0);
-#pragma unroll
-    for (int m = 0; m < nf; ++m) {
-        const R di = tab.D[i * nf + m], dj = tab.D[j * nf + m];
-        dxu += di * (su[m * nf + j] - ou);
-        dxv += di * (sv[m * nf + j] - ov);
-        deu += dj * (su[i * nf + m] - ou);
-        dev += dj * (sv[i * nf + m] - ov);
-    }
-    const R iw = tab.iw0;
-    // BR1 lift (U* - u)/w on the faces the node lies on
-    if (i == N) { dxu += (us[1 * nf + j] - u0) * iw; dxv += (vs[1 * nf + j] - v0) * iw; }
-    if (i == 0) { dxu -= (us[3 * nf + j] - u0) * iw; dxv -= (vs[3 * nf + j] - v0) * iw; }
-    if (j == N) { deu += (us[2 * nf + i] - u0) * iw; dev += (vs[2 * nf + i] - v0) * iw; }
-    if (j == 0) { deu -= (us[0 * nf + i] - u0) * iw; dev -= (vs[0 * nf + i] - v0) * iw; }
-    // J grad = (y_eta d_xi - y_xi d_eta, -x_eta d_xi + x_xi d_eta) = (Ax dxi + Ae deta, Cx dxi + Ce deta)
-    const R J = Ce * Ax - Cx * Ae;   // x_xi y_eta - x_eta y_xi
-    const R s = he / J;
-    Fv2 = s * (Ax * dxu + Ae * deu);
-    Gv2 = s * (Cx * dxu + Ce * deu);
-    Fv3 = s * (Ax * dxv + Ae * dev);
-    Gv3 = s * (Cx * dxv + Ce * dev);
-}
-
-// Indicator sweep over all elements (initial data, or after the state was
-// replaced): element viscosity, and the list of elements with eps > 0.
-template <int N, typename R>
-struct IndicatorArgs {
-    Phys<R> P;
-    Uni<R> tab;                  // uniform entries (read as scalars)
-    const Tab<R> *tg;            // the same tables in device memory: per-lane entries
-    int64_t K;
-    const R *h;
-    R *eps;             // [K]
-    int32_t *list;      // [K] elements with eps > 0 (order unspecified)
-    int *count;         // list length (zeroed beforehand)
-    int64_t ntiles;
-};
-
-template <int N, typename R>
-__global__ __launch_bounds__(Shape<N>::T) void indicator_kernel(IndicatorArgs<N, R> a)
-{
-    using S = Shape<N>;
-    constexpr int np = S::np, E = S::E, T = S::T;
-    __shared__ R s_h[T], s_red[6 * T], s_vinv[(N + 1) * (N + 1)];
-    __shared__ int s_any[T / 64];
-    const int64_t tile = xcd_tile(a.ntiles);
-    if (tile < 0) return;
-    const int t = threadIdx.x;
-    stage_vinv<N, R, T>(s_vinv, *a.tg, t);
-    const bool lane = t < E * np;
-    const int el = lane ? t / np : E - 1, p = lane ? t - el * np : 0;
-    const int64_t e = tile * E + el;
-    const bool act = lane && (e < a.K);
-    const R h = act ? a.h[e * np + p] : R(0);
-    s_h[t] = h;
-    lds_sync<T>();
-    R eps = R(0);
-    if (block_any_lds<T>(rough_line<N, R, E>(s_h, t, a.tab, a.P), s_any, t))
-        eps = element_viscosity<N, R>(s_h, s_red, s_vinv, a.P, t, el, p, lane, h);
-    if (act && p == 0) {
-        a.eps[e] = eps;
-        if (eps > R(0)) a.list[atomicAdd(a.count, 1)] = (int32_t)e;
-    }
-}
-
-// Work over the viscous-element list: groups of E listed elements per
-// iteration, grid-stride; an empty list exits at once.
-template <int N, typename R>
-struct ListArgs {
-    Mesh<R> m;
-    Phys<R> P;
-    Uni<R> tab;                  // uniform entries (read as scalars)
-    const Tab<R> *tg;            // the same tables in device memory: per-lane entries
-    const R *h, *hu, *hv;     // stage input state
-    const R *eps;             // [K] viscosity of this state
-    const int32_t *list;      // elements with eps > 0
-    const int *count;
-    R *vtr;                   // [K][4][nf][4] face viscous fluxes (pass 1 writes, pass 2 reads)
-    R *lv2, *lv3;             // [K][np] viscous terms (pass 2)
-    int *count_reset;         // pass 2: list counter of the next state, zeroed here
-};
-
-// Stage the listed elements' velocities and the BR1 interface states
-// U* = {u}, V* = {v} in LDS (shared by both passes).
-template <int N, typename R>
-__device__ __forceinline__ void load_viscous_element(const ListArgs<N, R> &a, int64_t g, int cnt, int t, int el,
-                                                     int p, bool lane, int64_t *s_e, R *s_h, R *s_u, R *s_v,
-                                                     R *s_us, R *s_vs, int64_t &e, R &h)
-{
-    using S = Shape<N>;
-    constexpr int nf = S::nf, np = S::np, E = S::E, T = S::T, NF = S::NFACE;
-    if (lane && p == 0) s_e[el] = (g * E + el < cnt) ? (int64_t)a.list[g * E + el] : int64_t(-1);
-    lds_sync<T>();
-    e = s_e[el];
-    const bool act = lane && e >= 0;
-    const int64_t q = e * np + p;
-    h = 0;
-    R u = 0, v = 0;
-    if (act) {
-        h = a.h[q];
-        const R ih = rcp_wet(h, a.P.h_tol);
-        u = a.hu[q] * ih;
-        v = a.hv[q] * ih;
-    }
-    s_h[t] = h;
-    s_u[t] = u;
-    s_v[t] = v;
-    lds_sync<T>();
-    for (int f = t; f < NF; f += T) {
-        const int fel = f / (4 * nf), s = (f / nf) & 3, k = f - (f / nf) * nf;
-        const int64_t fe = s_e[fel];
-        R us = 0, vs = 0;
-        if (fe >= 0) {
-            int fi, fj, ns, kk;
-            int64_t en;
-            side_node<N>(s, k, fi, fj);
-            const int lp = fel * np + fi * nf + fj;
-            const int64_t qn = nbr_node<N>(a.m, fe, s, k, en, ns, kk);
-            const R in = rcp_wet(a.h[qn], a.P.h_tol);
-            us = R(0.5) * (s_u[lp] + a.hu[qn] * in);
-            vs = R(0.5) * (s_v[lp] + a.hv[qn] * in);
-        }
-        s_us[f] = us;
-        s_vs[f] = vs;
-    }
-    lds_sync<T>();
-}
-
-// Pass 1: the physical viscous fluxes h eps (U1, V1), h eps (U2, V2) on the
-// faces of the listed elements (their neighbours' divergence needs them).
-template <int N, typename R>
-__global__ __launch_bounds__(Shape<N>::T) void av_faces_kernel(ListArgs<N, R> a)
-{
-    using S = Shape<N>;
-    constexpr int nf = S::nf, np = S::np, E = S::E, T = S::T, NF = S::NFACE;
-    __shared__ R s_h[T], s_u[T], s_v[T], s_us[NF], s_vs[NF];
-    __shared__ int64_t s_e[E];
-    const int cnt = *a.count;
-    const int t = threadIdx.x;
-    const bool lane = t < E * np;
-    const int el = lane ? t / np : E - 1, p = lane ? t - el * np : 0;
-    for (int64_t g = blockIdx.x; g * E < cnt; g += gridDim.x) {
-        int64_t e;
-        R h;
-        load_viscous_element<N, R>(a, g, cnt, t, el, p, lane, s_e, s_h, s_u, s_v, s_us, s_vs, e, h);
-        for (int f = t; f < NF; f += T) {
-            const int fel = f / (4 * nf), s = (f / nf) & 3, k = f - (f / nf) * nf;
-            const int64_t fe = s_e[fel];
-            if (fe < 0) continue;
-            int fi, fj;
-            side_node<N>(s, k, fi, fj);
-            const int lp = fel * np + fi * nf + fj;
-            const int64_t qo = fe * np + fi * nf + fj;
-            R Fv2, Fv3, Gv2, Gv3, oAx, oCx, oAe, oCe;
-            metric_at(a.m, qo, fe, oAx, oCx, oAe, oCe);
-            viscous_flux_at<N, R>(fi, fj, s_u + fel * np, s_v + fel * np, s_us + fel * 4 * nf,
-                                  s_vs + fel * 4 * nf, oAx, oCx, oAe, oCe, s_h[lp] * a.eps[fe], *a.tg, Fv2, Fv3,
-                                  Gv2, Gv3);
-            R *o = a.vtr + ((fe * 4 + s) * nf + k) * 4;
-            o[0] = Fv2;
-            o[1] = Fv3;
-            o[2] = Gv2;
-            o[3] = Gv3;
-        }
-        lds_sync<T>();
-    }
-}
-
-// Pass 2: the BR1 viscous divergence (Theorem 1, eq. ViscTermsDisc) L^v on
-// the momentum rows of the listed elements, interface fluxes averaged with
-// the neighbours' pass-1 fluxes (zero for neighbours without viscosity).
-// Elements without viscosity get their (face-only) viscous terms inside the
-// stage kernel.
-template <int N, typename R>
-__global__ __launch_bounds__(Shape<N>::T) void av_div_kernel(ListArgs<N, R> a)
-{
-    using S = Shape<N>;
-    constexpr int nf = S::nf, np = S::np, E = S::E, T = S::T, NF = S::NFACE;
-    __shared__ R s_h[T], s_u[T], s_v[T], s_us[NF], s_vs[NF], s_Fv[4][T], s_vn[4][NF];
-    __shared__ int64_t s_e[E];
-    if (a.count_reset && blockIdx.x == 0 && threadIdx.x == 0) *a.count_reset = 0;
-    const int cnt = *a.count;
-    const int t = threadIdx.x;
-    const bool lane = t < E * np;
-    const int el = lane ? t / np : E - 1, p = lane ? t - el * np : 0, i = p / nf, j = p - i * nf;
-    for (int64_t g = blockIdx.x; g * E < cnt; g += gridDim.x) {
-        int64_t e;
-        R h;
-        load_viscous_element<N, R>(a, g, cnt, t, el, p, lane, s_e, s_h, s_u, s_v, s_us, s_vs, e, h);
-        const bool act = lane && e >= 0;
-        const int64_t q = e * np + p;
-        // neighbours' face fluxes
-        for (int f = t; f < NF; f += T) {
-            const int fel = f / (4 * nf), s = (f / nf) & 3, k = f - (f / nf) * nf;
-            const int64_t fe = s_e[fel];
-            R n0 = 0, n1 = 0, n2 = 0, n3 = 0;
-            if (fe >= 0) {
-                int ns, kk;
-                int64_t en;
-                (void)nbr_node<N>(a.m, fe, s, k, en, ns, kk);
-                if (a.eps[en] > R(0)) {
-                    const R *vn = a.vtr + ((en * 4 + ns) * nf + kk) * 4;
-                    n0 = vn[0]; n1 = vn[1]; n2 = vn[2]; n3 = vn[3];
-                }
-            }
-            s_vn[0][f] = n0; s_vn[1][f] = n1; s_vn[2][f] = n2; s_vn[3][f] = n3;
-        }
-        R Ax = 0, Cx = 0, Ae = 0, Ce = 0, Fv2 = 0, Fv3 = 0, Gv2 = 0, Gv3 = 0;
-        if (act) {
-            metric_at(a.m, q, e, Ax, Cx, Ae, Ce);
-            viscous_flux_at<N, R>(i, j, s_u + el * np, s_v + el * np, s_us + el * 4 * nf, s_vs + el * 4 * nf,
-                                  Ax, Cx, Ae, Ce, h * a.eps[e], *a.tg, Fv2, Fv3, Gv2, Gv3);
-        }
-        // contravariant fluxes: F~v = J grad(xi) . (Fv, Gv), G~v = J grad(eta) . (Fv, Gv)
-        s_Fv[0][t] = Ax * Fv2 + Cx * Gv2;
-        s_Fv[1][t] = Ax * Fv3 + Cx * Gv3;
-        s_Fv[2][t] = Ae * Fv2 + Ce * Gv2;
-        s_Fv[3][t] = Ae * Fv3 + Ce * Gv3;
-        lds_sync<T>();
-        if (act) {
-            R Lv2 = 0, Lv3 = 0;
-            const int base = el * np;
-            // (single precision: over the jumps from the own fluxes, as in
-            // viscous_flux_at)
-            const R o0 = kJumpForm<R> ? s_Fv[0][t] : R(0), o1 = kJumpForm<R> ? s_Fv[1][t] : R(0);
-            const R o2 = kJumpForm<R> ? s_Fv[2][t] : R(0), o3 = kJumpForm<R> ? s_Fv[3][t] : R(0);
-#pragma unroll
-            for (int mm = 0; mm < nf; ++mm) {
-                const R di = a.tg->D[i * nf + mm], dj = a.tg->D[j * nf + mm];
-                Lv2 += di * (s_Fv[0][base + mm * nf + j] - o0) + dj * (s_Fv[2][base + i * nf + mm] - o2);
-                Lv3 += di * (s_Fv[1][base + mm * nf + j] - o1) + dj * (s_Fv[3][base + i * nf + mm] - o3);
-            }
-            // faces: (1/(2 w_0)) n_s . (Fv_nbr - Fv_own), n_s outward scaled normal
-            const R hw = R(0.5) * a.tab.iw0;
-            const int fb = el * 4 * nf;
-            auto face = [&](int s, int k, R snx, R sny) {
-                const int f = fb + s * nf + k;
-                Lv2 += hw * (snx * (s_vn[0][f] - Fv2) + sny * (s_vn[2][f] - Gv2));
-                Lv3 += hw * (snx * (s_vn[1][f] - Fv3) + sny * (s_vn[3][f] - Gv3));
-            };
-            if (j == 0) face(0, i, -Ae, -Ce);
-            if (i == N) face(1, j, Ax, Cx);
-            if (j == N) face(2, i, Ae, Ce);
-            if (i == 0) face(3, j, -Ax, -Cx);
-            a.lv2[q] = Lv2;
-            a.lv3[q] = Lv3;
-        }
-        lds_sync<T>();
-    }
-}
-
 // ------------------------------------------------------------------------
 // Stage kernel
 // ------------------------------------------------------------------------
@@ -1219,11 +966,8 @@ struct StageArgs {
     int store_du;                // 0 on the last LSRK stage: the next step's first stage does not read dU
     // artificial viscosity (nullptr eps: off)
     const R *eps;                // [K] viscosity of the input state
-    const R *vtr;                // [K][4][nf][4] face viscous fluxes of viscous elements
-    const R *lv2, *lv3;          // [K][np] viscous terms of viscous elements
-    R *eps_out;                  // [K] viscosity of the output state (update modes)
-    int32_t *list_out;           // elements of the output state with eps > 0
-    int *count_out;
+    const R *vfl;                // [K][4][nf][2] face_parts of its elements with viscosity
+    R *eps_out, *vfl_out;        // the same of the output state (update modes)
     R *dtc_out, *dtv_out;        // last stage of a step: per-element CFL / viscous bounds of the output
     R *frec_out;                 // with them (limiter on): face records [K][4][nf][3] (h, u, v) of the output
     const int32_t *inst;         // [K] instance of each element (ensembles), nullptr: one instance
@@ -1238,6 +982,181 @@ struct StageArgs {
     int variant;                 // compiled variant 0..kStageVariants-1 (launch side)
 };
 
+// ---- artificial viscosity (Theorem 1, eq. BR1) ----
+// The viscous flux h eps grad u of an element needs the derivatives of its
+// own velocities and, on its sides, the jumps U* - u = (u_nbr - u) / 2.  Its
+// neighbours need n . (h eps grad u) on the shared sides.  The part without
+// the jumps is known where the element's state is: whoever computes a viscosity
+// eps > 0 (the stage kernel's epilogue, the indicator pass) leaves it per face
+// node (face_parts), and the next stage kernel adds the jumps to it
+// (nbr_viscous_flux) and forms the element's own divergence from its staged
+// velocities.  So a stage is one launch: with the viscous fluxes and their
+// divergence in two passes of their own, over a list of elements, most often
+// empty, each stage spent two more launches of 4.6-5 us.
+
+// Derivatives along both lines through node (i, j) of a pair of staged
+// values: the D rows from the zero-diagonal table dz, whose missing diagonal
+// is -+N(N+1)/4 at the ends and zero between; at(i, j) returns the pair.
+// Single precision sums over the jumps from the node's own values (D's rows
+// sum to zero), so that neither the rounding of the table's row sums nor that
+// of products at the size of the values themselves enters (kJumpForm).
+template <int N, typename R, typename At>
+__device__ __forceinline__ void line_derivatives(const R *dz, int i, int j, const At &at, typename Vec2<R>::type own,
+                                                 R &dx1, R &dx2, R &de1, R &de2)
+{
+    constexpr int nf = N + 1;
+    constexpr R end = R(0.25) * R(N * (N + 1));
+    const R o1 = kJumpForm<R> ? own.x : R(0), o2 = kJumpForm<R> ? own.y : R(0);
+    dx1 = dx2 = de1 = de2 = R(0);
+#pragma unroll 2
+    for (int m = 0; m < nf; ++m) {
+        R di = dz[i * nf + m], dj = dz[j * nf + m];
+        if constexpr (!kJumpForm<R>) {
+            if (m == i) di = i == N ? end : (i == 0 ? -end : R(0));
+            if (m == j) dj = j == N ? end : (j == 0 ? -end : R(0));
+        }
+        const auto a = at(m, j), b = at(i, m);
+        dx1 += di * (a.x - o1);
+        dx2 += di * (a.y - o2);
+        de1 += dj * (b.x - o1);
+        de2 += dj * (b.y - o2);
+    }
+}
+
+// n . (h eps grad u), n . (h eps grad v) without the side jumps at node
+// (i, j) of element e, n the outward scaled normal, for each side that the
+// node lies on, to vfl [K][4][nf][2].  he: h eps at the node.
+template <int N, typename R, typename At>
+__device__ __forceinline__ void face_parts(R *vfl, const R *dz, int64_t e, int i, int j, const At &at,
+                                           typename Vec2<R>::type own, R he, R Ax, R Cx, R Ae, R Ce)
+{
+    constexpr int nf = N + 1;
+    R dxu, dxv, deu, dev;
+    line_derivatives<N, R>(dz, i, j, at, own, dxu, dxv, deu, dev);
+    const R sc = he / (Ce * Ax - Cx * Ae);
+    const R aa = sc * (Ax * Ax + Cx * Cx), ae = sc * (Ax * Ae + Cx * Ce), ee = sc * (Ae * Ae + Ce * Ce);
+    const R xu = aa * dxu + ae * deu, xv = aa * dxv + ae * dev;   // normal (Ax, Cx)
+    const R yu = ae * dxu + ee * deu, yv = ae * dxv + ee * dev;   // normal (Ae, Ce)
+    auto rec = [&](int s, int k, R a, R b) {
+        R *const r = vfl + ((e * 4 + s) * nf + k) * 2;
+        r[0] = a;
+        r[1] = b;
+    };
+    if (j == 0) rec(0, i, -yu, -yv);
+    if (i == N) rec(1, j, xu, xv);
+    if (j == N) rec(2, i, yu, yv);
+    if (i == 0) rec(3, j, -xu, -xv);
+}
+
+// Half the jump of (u, v) across side s at node k of element e, whose own
+// velocities there are (u0, v0): U* - u, V* - v (zero at a wall, which names
+// the node itself).
+template <int N, typename R>
+__device__ __forceinline__ void side_jump(const StageArgs<R> &a, int64_t e, int s, int k, R u0, R v0, R &ju, R &jv)
+{
+    int64_t en;
+    int ns, kk;
+    const int64_t qn = nbr_node<N>(a.m, e, s, k, en, ns, kk);
+    const R in = rcp_wet(a.h[qn], a.P.h_tol);
+    ju = R(0.5) * (a.hu[qn] * in - u0);
+    jv = R(0.5) * (a.hv[qn] * in - v0);
+}
+
+// n . (h eps grad u), n . (h eps grad v) of element e (eps > 0) at node k of
+// its side s, n its outward scaled normal, with the velocities (uo, vo) across
+// the side.
+template <int N, typename R>
+__device__ __forceinline__ void nbr_viscous_flux(const StageArgs<R> &a, int64_t e, int s, int k, R uo, R vo, R &fu,
+                                                 R &fv)
+{
+    constexpr int nf = N + 1, np = nf * nf;
+    int i, j;
+    side_node<N>(s, k, i, j);
+    const R *const r = a.vfl + ((e * 4 + s) * nf + k) * 2;
+    fu = r[0];
+    fv = r[1];
+    const int64_t q = e * np + i * nf + j;
+    R Ax, Cx, Ae, Ce;
+    metric_at(a.m, q, e, Ax, Cx, Ae, Ce);
+    const R h = a.h[q], ih = rcp_wet(h, a.P.h_tol), u = a.hu[q] * ih, v = a.hv[q] * ih;
+    const R sc = a.tab.iw0 * h * a.eps[e] / (Ce * Ax - Cx * Ae);
+    const R aa = sc * (Ax * Ax + Cx * Cx), ae = sc * (Ax * Ae + Cx * Ce), ee = sc * (Ae * Ae + Ce * Ce);
+    // the jump across a side enters the derivative along its normal with the
+    // side's sign, and n . the metric once more: squared on the side itself
+    const R d = (s & 1) ? aa : ee;
+    fu += d * R(0.5) * (uo - u);
+    fv += d * R(0.5) * (vo - v);
+    // a corner also lies on a side of the other direction
+    const int t = (s & 1) ? (j == N ? 2 : (j == 0 ? 0 : -1)) : (i == N ? 1 : (i == 0 ? 3 : -1));
+    if (t >= 0) {
+        R ju, jv;
+        side_jump<N>(a, e, t, (s & 1) ? i : j, u, v, ju, jv);
+        const bool pos = ((s == 1 || s == 2) == (t == 1 || t == 2));
+        fu += (pos ? ae : -ae) * ju;
+        fv += (pos ? ae : -ae) * jv;
+    }
+}
+
+// Indicator sweep over all elements (initial data, or after the state was
+// replaced): element viscosity and the viscous face fluxes' own part.
+template <int N, typename R>
+struct IndicatorArgs {
+    Phys<R> P;
+    Uni<R> tab;                  // uniform entries (read as scalars)
+    const Tab<R> *tg;            // the same tables in device memory: per-lane entries
+    int64_t K;
+    Mesh<R> m;
+    const R *h, *hu, *hv;
+    R *eps;             // [K]
+    R *vfl;             // [K][4][nf][2]
+    int64_t ntiles;
+};
+
+template <int N, typename R>
+__global__ __launch_bounds__(Shape<N>::T) void indicator_kernel(IndicatorArgs<N, R> a)
+{
+    using S = Shape<N>;
+    constexpr int np = S::np, E = S::E, T = S::T;
+    __shared__ __align__(16) R s_red[6 * T];
+    __shared__ R s_h[T], s_vinv[(N + 1) * (N + 1)];
+    __shared__ int s_any[2][T / 64];
+    const int64_t tile = xcd_tile(a.ntiles);
+    if (tile < 0) return;
+    const int t = threadIdx.x;
+    stage_vinv<N, R, T>(s_vinv, *a.tg, t);
+    const bool lane = t < E * np;
+    const int el = lane ? t / np : E - 1, p = lane ? t - el * np : 0;
+    const int64_t e = tile * E + el;
+    const bool act = lane && (e < a.K);
+    const R h = act ? a.h[e * np + p] : R(0);
+    s_h[t] = h;
+    lds_sync<T>();
+    R eps = R(0);
+    if (block_any_lds<T>(rough_line<N, R, E>(s_h, t, a.tab, a.P), s_any[0], t))
+        eps = element_viscosity<N, R>(s_h, s_red, s_vinv, a.P, t, el, p, lane, h);
+    if (act && p == 0) a.eps[e] = eps;
+    // (as in the stage kernel's epilogue)
+    if (!block_any_lds<T>(act && p == 0 && eps > R(0), s_any[1], t)) return;
+    using V2 = typename Vec2<R>::type;
+    V2 *const s_w = (V2 *)s_red;
+    const int64_t q = e * np + p;
+    const R ih = rcp_wet(h, a.P.h_tol);
+    const V2 w = act ? V2{a.hu[q] * ih, a.hv[q] * ih} : V2{R(0), R(0)};
+    lds_sync<T>();
+    if (lane && p == 0) s_h[el * np] = eps;
+    s_w[t] = w;
+    for (int c = t; c < np; c += T) s_vinv[c] = a.tg->Dz[c];
+    lds_sync<T>();
+    const int i = p / (N + 1), j = p - i * (N + 1);
+    const R ev = s_h[el * np];
+    if (act && ev > R(0) && (i == 0 || i == N || j == 0 || j == N)) {
+        R Ax, Cx, Ae, Ce;
+        metric_at(a.m, q, e, Ax, Cx, Ae, Ce);
+        face_parts<N, R>(a.vfl, s_vinv, e, i, j, [&](int r, int c) { return s_w[el * np + r * (N + 1) + c]; }, w,
+                         h * ev, Ax, Cx, Ae, Ce);
+    }
+}
+
 // Face slot data loaded ahead of the LDS staging (slots t, t + T, ... of lane t).
 // Kept small (it is live across the LDS staging): the neighbour element and
 // one packed word.
@@ -1248,7 +1167,7 @@ struct FacePrefetch {
     R h = 0, hu = 0, hv = 0, bo = 0, bn = 0;
     __device__ int ns() const { return code & 3; }
     __device__ int kk() const { return (code >> 2) & 63; }
-    // with AV: the element has no viscosity, its neighbour has
+    // with AV: the neighbour (not a wall) has viscosity
     __device__ bool visc_nbr() const { return (code >> 8) & 1; }
     __device__ bool wall() const { return (code >> 9) & 1; }
 };
@@ -1274,7 +1193,7 @@ __device__ __forceinline__ void prefetch_face(const StageArgs<R> &a, int f, int6
         pf.hv = a.hv[qn];
     }
     pf.bn = a.m.bface[(uint64_t)(uint32_t)en * (4 * nf) + (uint32_t)(ns * nf + kk)];
-    const bool vn = a.eps && !((a.eps + e0)[fel] > R(0)) && a.eps[en] > R(0);
+    const bool vn = a.eps && !(c & 8) && a.eps[en] > R(0);
     pf.en = en;
     pf.code = ns | (kk << 2) | ((int)vn << 8) | ((c & 8) << 6);
 }
@@ -1301,7 +1220,7 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
     R *const s_h = s_st + 8 * LEN;
     __shared__ R s_fl[3][NF];
     __shared__ R s_lim[4 * E];
-    __shared__ int s_any[2][T / 64];    // block_any_lds
+    __shared__ int s_any[4][T / 64];    // block_any_lds
     __shared__ R s_dz[nf * nf];         // D with a zero diagonal (volume term)
     __shared__ R s_mref[kMetricRel<R> ? 4 * E : 1];  // the tile elements' Mesh::mref (single precision)
 
@@ -1362,7 +1281,9 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
     FacePrefetch<R> pf0;
     // (a one-trip loop here costs a VGPR and a dozen spilled SGPRs at N = 7)
     prefetch_face<N, R, E, NF>(a, t, e0, pf0);
-    const R eps_e = (av && act) ? a.eps[e] : R(0);
+    // has this lane's element viscosity (a lane mask; the value itself is
+    // read again where it is used)
+    const bool visc = av && act && (a.eps + e0)[el] > R(0);
     const R ih = rcp_wet(h, P.h_tol);
     const R u = hu * ih, v = hv * ih;
     const int st = lane ? el * PS + i * RS + stage_col<N, V>(i, j) : E * PS + (t - E * np);
@@ -1400,9 +1321,9 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
     if (t < nf * nf) s_dz[t] = dz_t;
     lds_sync<T>();
 
-    // ---- interface: (1/w_0) J^surf F*(own, nbr, n_out) per face node; for
-    // an element without viscosity next to one with viscosity, also its only
-    // viscous term: (1/(2 w_0)) n_s . Fv_nbr (its own viscous fluxes are 0) ----
+    // ---- interface: (1/w_0) J^surf F*(own, nbr, n_out) per face node, and
+    // next to an element with viscosity the neighbour's half of the mean
+    // viscous flux, (1/(2 w_0)) n . Fv_nbr with the neighbour's normal in L ----
     auto face_slot = [&](const int f, const FacePrefetch<R> &pfr) {
         const int side = f / nf, fel = side / 4, s = side & 3, k = f - side * nf;
         R c0 = 0, c1 = 0, c2 = 0;
@@ -1454,11 +1375,14 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
             // (zero for a continuous bottom and at walls, where bn = bo)
             const R pen = R(0.25) * P.g * a.tab.iw0 * (s_h[lp] + hn) * (bn - bo);
             c1 += pen * snx; c2 += pen * sny;
-            if (av && pfr.visc_nbr()) {
-                const R *vn = a.vtr + (((int64_t)pfr.en * 4 + pfr.ns()) * nf + pfr.kk()) * 4;
-                const R hw = R(0.5) * a.tab.iw0;
-                c1 -= hw * (snx * vn[0] + sny * vn[2]);
-                c2 -= hw * (snx * vn[1] + sny * vn[3]);
+            if (__builtin_expect(av && pfr.visc_nbr(), 0)) {
+                const StageArgs<R> &va = kernarg<StageArgs<R>>();
+                R fu, fv;
+                const V2 wo = s_w[lp];
+                nbr_viscous_flux<N, R>(va, pfr.en, pfr.ns(), pfr.kk(), wo.x, wo.y, fu, fv);
+                const R hw = R(0.5) * va.tab.iw0;
+                c1 += hw * fu;
+                c2 += hw * fv;
             }
         }
         s_fl[0][f] = c0; s_fl[1][f] = c1; s_fl[2][f] = c2;
@@ -1571,6 +1495,14 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
             C3 += dh * sC;
         }
     }
+    {
+    // the lane's place in the tile once more (see fresh): kept across the
+    // volume sums, the indices spilled at N = 4 and 6
+    const int t = kFreshLanes<N, R> ? fresh(threadIdx.x) : (int)threadIdx.x;
+    const int el = lane ? t / np : E - 1, p = lane ? t - el * np : 0, i = p / nf, j = p - i * nf;
+    const int st = lane ? el * PS + i * RS + stage_col<N, V>(i, j) : E * PS + (t - E * np);
+    const int64_t e = e0 + el;
+    const uint32_t tq = act ? (uint32_t)t : 0u;
     const R h2g = R(2) * P.g * h;
     // (the jump form's mass sum enters the momentum sums twice: 2u dF1)
     const R uA = kJumpForm<R> ? R(2) * u : u, vA = kJumpForm<R> ? R(2) * v : v;
@@ -1597,8 +1529,72 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
     const StageArgs<R> &late = kernarg<StageArgs<R>>();
     const Phys<R> &PL = late.P;
     const R bxv = (late.m.bx + q0)[tq], byv = (late.m.by + q0)[tq];
+    // ---- viscous divergence of the elements with viscosity (eq.
+    // ViscTermsDisc, interface fluxes {F^v}): from the staged velocities, the
+    // contravariant fluxes staged in place of the metric directions.  An
+    // element without viscosity has no viscous flux of its own; the
+    // neighbours' halves came with the face slots ----
     R Lv2 = 0, Lv3 = 0;
-    if (av && eps_e > R(0)) { Lv2 = (late.lv2 + q0)[tq]; Lv3 = (late.lv3 + q0)[tq]; }
+    // (the update's operands too are read ahead of the branch, behind which
+    // their latency would be paid once more)
+    R w0 = 0, w1 = 0, w2 = 0;   // LSRK: the register dU; SSP: W^n
+    if constexpr (MODE == kModeLsrk) {
+        // the first stage has a_1 = 0: the register is not read
+        if (late.ca != R(0)) { w0 = (late.dh + q0)[tq]; w1 = (late.dhu + q0)[tq]; w2 = (late.dhv + q0)[tq]; }
+    } else if constexpr (MODE == kModeSsp) {
+        w0 = (late.h0 + q0)[tq]; w1 = (late.hu0 + q0)[tq]; w2 = (late.hv0 + q0)[tq];
+    }
+    if (av && __builtin_expect(block_any_lds<T>(visc, s_any[2], t), 0)) {
+        const int base = el * PS;
+        V2 fa = V2{R(0), R(0)}, fb = fa;
+        if (visc) {
+            const R eps_e = (late.eps + e0)[el];
+            R dxu, dxv, deu, dev;
+            line_derivatives<N, R>(s_dz, i, j, [&](int r, int c) { return s_w[base + r * RS + stage_col<N, V>(r, c)]; },
+                                   V2{u, v}, dxu, dxv, deu, dev);
+            const R iw = late.tab.iw0;
+            auto lift = [&](int s, int k, R &du, R &dv, R sg) {
+                R ju, jv;
+                side_jump<N>(late, e, s, k, u, v, ju, jv);
+                du += sg * ju;
+                dv += sg * jv;
+            };
+            if (i == N) lift(1, j, dxu, dxv, iw);
+            if (i == 0) lift(3, j, dxu, dxv, -iw);
+            if (j == N) lift(2, i, deu, dev, iw);
+            if (j == 0) lift(0, i, deu, dev, -iw);
+            // contravariant fluxes J grad(xi) . (h eps grad), J grad(eta) . (...)
+            const R sc = h * eps_e / J;
+            const R aa = sc * (Ax * Ax + Cx * Cx), ae = sc * (Ax * Ae + Cx * Ce), ee = sc * (Ae * Ae + Ce * Ce);
+            fa = V2{aa * dxu + ae * deu, aa * dxv + ae * dev};
+            fb = V2{ae * dxu + ee * deu, ae * dxv + ee * dev};
+        }
+        s_a[st] = fa;
+        s_b[st] = fb;
+        lds_sync<T>();
+        if (visc) {
+            R ax, ay, bx, by;
+            R x1, x2, y1, y2;
+            line_derivatives<N, R>(s_dz, i, j, [&](int r, int c) { return s_a[base + r * RS + stage_col<N, V>(r, c)]; },
+                                   fa, ax, ay, x1, x2);
+            line_derivatives<N, R>(s_dz, i, j, [&](int r, int c) { return s_b[base + r * RS + stage_col<N, V>(r, c)]; },
+                                   fb, y1, y2, bx, by);
+            Lv2 = ax + bx;
+            Lv3 = ay + by;
+            // the own half at the faces, -(1/(2 w_0)) n . Fv (none at a wall)
+            const R hw = R(0.5) * late.tab.iw0;
+            auto face = [&](int s, V2 f, R sg) {
+                if (is_wall(late.m, e, s)) return;
+                Lv2 -= sg * f.x;
+                Lv3 -= sg * f.y;
+            };
+            if (j == 0) face(0, fb, -hw);
+            if (i == N) face(1, fa, hw);
+            if (j == N) face(2, fb, hw);
+            if (i == 0) face(3, fa, -hw);
+        }
+        lds_sync<T>();
+    }
     const R iJ = act ? rcp_nr(J) : R(0);
     const R hg = R(0.5) * PL.g * h;
     const R R1 = -L1 * iJ;
@@ -1613,14 +1609,11 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
         R nh, nhu, nhv;
         R d0 = 0, d1 = 0, d2 = 0;
         if constexpr (MODE == kModeLsrk) {
-            // the first stage has a_1 = 0: the register is not read
-            if (late.ca != R(0)) { d0 = (late.dh + q0)[tq]; d1 = (late.dhu + q0)[tq]; d2 = (late.dhv + q0)[tq]; }
-            d0 = late.ca * d0 + dt * R1;
-            d1 = late.ca * d1 + dt * R2;
-            d2 = late.ca * d2 + dt * R3;
+            d0 = late.ca * w0 + dt * R1;
+            d1 = late.ca * w1 + dt * R2;
+            d2 = late.ca * w2 + dt * R3;
             nh = h + late.cb * d0; nhu = hu + late.cb * d1; nhv = hv + late.cb * d2;
         } else {
-            const R w0 = (late.h0 + q0)[tq], w1 = (late.hu0 + q0)[tq], w2 = (late.hv0 + q0)[tq];
             nh = late.ca * w0 + late.cb * (h + dt * R1);
             nhu = late.ca * w1 + late.cb * (hu + dt * R2);
             nhv = late.ca * w2 + late.cb * (hv + dt * R3);
@@ -1628,7 +1621,7 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
         // positivity limiter (eq. PosPres) toward the J-weighted means; an
         // element without a negative node keeps theta = 1, so the means are
         // only formed when some element of the workgroup has one
-        if (PL.limiter_on && block_any_lds<T>(act && nh < R(0), s_any[0], t)) {
+        if (PL.limiter_on && __builtin_expect(block_any_lds<T>(act && nh < R(0), s_any[0], t), 0)) {
             const R wq = act ? J * late.tg->w[i] * late.tg->w[j] : R(0);
             R vals[5] = {wq, wq * nh, wq * nhu, wq * nhv, act ? nh : R(3.0e38)};
             elem_totals_any<N, R, 5, true, T>(vals, s_st, t, el, p, lane);
@@ -1674,16 +1667,29 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
             // viscosity of the new state for the next stage (appendix A)
             s_st[8 * T + t] = nh;
             lds_sync<T>();
-            if (block_any_lds<T>(rough_line<N, R, E>(s_st + 8 * T, t, late.tab, PL), s_any[1], t)) {
+            if (__builtin_expect(block_any_lds<T>(rough_line<N, R, E>(s_st + 8 * T, t, late.tab, PL), s_any[1], t), 0)) {
                 static_assert(2 * T >= nf * nf, "V^{-1} between the reduction scratch and the heights");
                 R *const s_vinv = s_st + 6 * T;
                 if (t < nf * nf) s_vinv[t] = late.tg->Vinv[t];
                 lds_sync<T>();
                 en = element_viscosity<N, R, T>(s_st + 8 * T, s_st, s_vinv, PL, t, el, p, lane, nh);
             }
-            if (act && p == 0) {
-                late.eps_out[e] = en;
-                if (en > R(0)) late.list_out[atomicAdd(late.count_out, 1)] = (int32_t)e;
+            if (act && p == 0) late.eps_out[e] = en;
+            // the viscous face fluxes' own part for the next stage
+            if (__builtin_expect(block_any_lds<T>(act && p == 0 && en > R(0), s_any[3], t), 0)) {
+                V2 *const s_nw = (V2 *)s_st;   // velocities of the new state
+                const R ihn = rcp_wet(nh, PL.h_tol);
+                const V2 nw = V2{nhu * ihn, nhv * ihn};
+                lds_sync<T>();
+                if (lane && p == 0) s_lim[el] = en;
+                s_nw[t] = nw;
+                lds_sync<T>();
+                const R ev = s_lim[el];
+                if (act && ev > R(0) && (i == 0 || i == N || j == 0 || j == N))
+                    face_parts<N, R>(late.vfl_out, s_dz, e, i, j,
+                                     [&](int r, int c) { return s_nw[el * np + r * nf + c]; }, nw, nh * ev, Ax, Cx,
+                                     Ae, Ce);
+                lds_sync<T>();
             }
         }
         if (late.dtc_out) {
@@ -1714,6 +1720,7 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
                 if (late.dtv_out) late.dtv_out[e] = en > R(0) ? visc_bound<R>(en, late.gmax[e], PL) : R(3.0e38);
             }
         }
+    }
     }
 }
 

@@ -30,10 +30,8 @@ struct Bufs {
     void *frec = nullptr;    // [K][4][nf][3] face records (h, u, v) of the state whose bounds are in dtc
     void *dtc = nullptr, *dtv = nullptr;  // [K] per-element CFL / viscous bounds of one state
     void *eps[3] = {};       // [K] element viscosity of each state buffer
-    int32_t *list[3] = {};   // [K] elements of each state buffer with eps > 0
-    int *count = nullptr;    // [3] list lengths
-    void *vtr = nullptr;     // [K][4][nf][4] viscous face fluxes (elements with eps > 0)
-    void *lv[2] = {};        // [K][np] viscous terms L^v (momentum rows)
+    void *vfl[3] = {};       // [K][4][nf][2] own part of the viscous face fluxes of those with eps > 0
+    int *count = nullptr;    // number of elements with eps > 0 (esdg_step_stats)
     double *dscal = nullptr; // per instance k: [8k..8k+3] dt and its bounds, [8k+4] time, [8k+5..7] spare
     unsigned long long *slots = nullptr;  // [instance][3][kDtSlots]
     int n_inst = 1;          // instances (ensembles); > 1: the arrays below are set
@@ -55,7 +53,7 @@ struct Ev {
 
 struct StageCall {
     int mode;          // kModeRhs, kModeLsrk, kModeSsp
-    bool av;           // add the viscous terms of visc()
+    bool av;           // add the viscous terms
     int in, out, base; // state buffers: input, output, W^n (SSP)
     bool out_rhs;      // write into Rb instead of W[out]
     double ca, cb;     // stage coefficients
@@ -82,9 +80,6 @@ struct Launch {
     static hipError_t bathymetry(const Bufs &B, const double *b, const Tab<double> &td, hipStream_t s);
     static hipError_t indicator(const Bufs &B, int buf, const Phys<R> &P, const Tab<R> &t, hipStream_t s,
                                 Ev ev);
-    static hipError_t av_faces(const Bufs &B, int in, const Phys<R> &P, const Tab<R> &t, hipStream_t s, Ev ev);
-    static hipError_t av_div(const Bufs &B, int in, int reset, const Phys<R> &P, const Tab<R> &t,
-                             hipStream_t s, Ev ev);
     static hipError_t stage(const Bufs &B, const StageCall &c, const Phys<R> &P, const Tab<R> &t,
                             hipStream_t s, Ev ev);
     static hipError_t limit(const Bufs &B, int buf, const Phys<R> &P, const Tab<R> &t, hipStream_t s);

@@ -76,13 +76,13 @@ __global__ void fill_int_kernel(int *p, int v, int n)
     if (t < n) p[t] = v;
 }
 
-// The viscous-element list of a state from its element viscosities (count
-// zeroed beforehand; the list order does not matter to the viscous passes).
+// Number of elements with viscosity, added to *count.
 template <typename R>
-__global__ void relist_kernel(const R *eps, int32_t *list, int *count, int64_t K)
+__global__ void count_viscous_kernel(const R *eps, int *count, int64_t K)
 {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < K && eps[e] > R(0)) list[atomicAdd(count, 1)] = (int32_t)e;
+    const uint64_t m = __ballot(e < K && eps[e < K ? e : 0] > R(0));
+    if ((threadIdx.x & 63) == 0 && m) atomicAdd(count, __popcll(m));
 }
 
 // Step status flags: [0] negative element mean, [1] limited elements,
@@ -434,8 +434,8 @@ void free_bufs(esdg_ctx *c)
     ++c->graph_gen;
     Bufs &B = c->B;
     void *ps[] = {B.x, B.y, B.xr, B.yr, B.mref, B.Ax, B.Cx, B.Ae, B.Ce, B.bx, B.by, B.bface, B.b, B.nbr, B.code, B.count,
-                  B.vtr, B.gmax, B.dtc, B.dtv, B.fgeo, B.frec, B.tabg, B.lv[0], B.lv[1], B.dscal, B.slots, B.flags, B.part, c->stage_d,
-                  B.eps[0], B.eps[1], B.eps[2], B.list[0], B.list[1], B.list[2], B.inst, B.cstart, B.cinst,
+                  B.gmax, B.dtc, B.dtv, B.fgeo, B.frec, B.tabg, B.dscal, B.slots, B.flags, B.part, c->stage_d,
+                  B.eps[0], B.eps[1], B.eps[2], B.vfl[0], B.vfl[1], B.vfl[2], B.inst, B.cstart, B.cinst,
                   B.iflags, B.imask};
     for (void *p : ps)
         if (p) (void)hipFree(p);
@@ -488,20 +488,18 @@ int timed(esdg_ctx *ctx, int cls, F &&launch)
     return ESDG_OK;
 }
 
-// Derived per-state data (viscosity, viscous list, dt bounds) is stale.
+// Derived per-state data (viscosity, viscous face fluxes, dt bounds) is stale.
 void invalidate_eps(esdg_ctx *ctx)
 {
     for (bool &v : ctx->eps_valid) v = false;
     ctx->dtb_buf = -1;
 }
 
-// Element viscosity and viscous-element list of state buffer buf, when stale
+// Element viscosity of state buffer buf, when stale
 // (the stage kernel keeps them current for the states it writes).
 int ensure_eps(esdg_ctx *ctx, int buf)
 {
     if (ctx->eps_valid[buf]) return ESDG_OK;
-    hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(64), 0, ctx->stream, ctx->B.count + buf, 0, 1);
-    CK(hipGetLastError());
     TRY(timed(ctx, kProfIndicator, [&](Ev ev) {
         return dispatch(ctx, [&](auto L, auto r) {
             using R = decltype(r);
@@ -510,25 +508,6 @@ int ensure_eps(esdg_ctx *ctx, int buf)
     }));
     ctx->eps_valid[buf] = true;
     return ESDG_OK;
-}
-
-// Viscous terms of the listed elements of state buffer buf (both passes);
-// reset >= 0 zeroes that buffer's list counter for the stage about to run.
-int launch_viscous(esdg_ctx *ctx, int buf, int reset)
-{
-    TRY(ensure_eps(ctx, buf));
-    TRY(timed(ctx, kProfAvFaces, [&](Ev ev) {
-        return dispatch(ctx, [&](auto L, auto r) {
-            using R = decltype(r);
-            return decltype(L)::av_faces(ctx->B, buf, phys<R>(ctx), tab<R>(ctx), ctx->stream, ev);
-        });
-    }));
-    return timed(ctx, kProfAvDiv, [&](Ev ev) {
-        return dispatch(ctx, [&](auto L, auto r) {
-            using R = decltype(r);
-            return decltype(L)::av_div(ctx->B, buf, reset, phys<R>(ctx), tab<R>(ctx), ctx->stream, ev);
-        });
-    });
 }
 
 int launch_stage(esdg_ctx *ctx, StageCall sc)
@@ -681,7 +660,7 @@ int launch_one_step(esdg_ctx *ctx, double dt, bool with_dt = true)
     int in = base;
     for (int k = 0; k < nst; ++k) {
         const int out = (k % 2 == 0) ? o1 : o2;
-        if (av) TRY(launch_viscous(ctx, in, out));
+        if (av) TRY(ensure_eps(ctx, in));
         const bool last = k == nst - 1;
         StageCall sc = ssp ? StageCall{kModeSsp, av, in, out, base, false, kSspAlpha[k], kSspBeta[k], last}
                            : StageCall{kModeLsrk, av, in, out, base, false, kLsrkA[k], kLsrkB[k], last, !last};
@@ -784,7 +763,7 @@ int graph_step(esdg_ctx *ctx, double dt)
 
 int run_rhs(esdg_ctx *ctx, int buf)
 {
-    if (ctx->P.av_on) TRY(launch_viscous(ctx, buf, -1));
+    if (ctx->P.av_on) TRY(ensure_eps(ctx, buf));
     StageCall sc{kModeRhs, ctx->P.av_on != 0, buf, buf, buf, true, 0.0, 0.0, false};
     return launch_stage(ctx, sc);
 }
@@ -1013,6 +992,7 @@ int upload_mesh_impl(esdg_ctx *ctx, int N, int64_t K, const double *x, const dou
     TRY(alloc(ctx, &B.nbr, K * 4 * sizeof(int32_t)));
     TRY(alloc(ctx, &B.code, K * 4));
     for (void *&p : B.eps) TRY(alloc(ctx, &p, K * r));
+    for (void *&p : B.vfl) TRY(alloc(ctx, &p, K * 4 * nf * 2 * r));
     TRY(alloc(ctx, &B.gmax, K * r));
     TRY(alloc(ctx, &B.dtc, K * r));
     TRY(alloc(ctx, &B.dtv, K * r));
@@ -1023,11 +1003,7 @@ int upload_mesh_impl(esdg_ctx *ctx, int N, int64_t K, const double *x, const dou
         CK(hipMemcpyAsync(B.tabg, &ctx->td, sizeof(Tab<double>), hipMemcpyHostToDevice, ctx->stream));
     else
         CK(hipMemcpyAsync(B.tabg, &ctx->tf, sizeof(Tab<float>), hipMemcpyHostToDevice, ctx->stream));
-    for (int32_t *&p : B.list) TRY(alloc(ctx, &p, K * sizeof(int32_t)));
-    TRY(alloc(ctx, &B.count, 4 * sizeof(int)));
-    TRY(alloc(ctx, &B.lv[0], n * r));
-    TRY(alloc(ctx, &B.lv[1], n * r));
-    TRY(alloc(ctx, &B.vtr, K * 4 * nf * 4 * r));
+    TRY(alloc(ctx, &B.count, sizeof(int)));
     TRY(alloc(ctx, &B.dscal, 8 * ni * sizeof(double)));
     TRY(alloc(ctx, &B.slots, (size_t)3 * kDtSlots * ni * sizeof(unsigned long long)));
     B.n_inst = ni;
@@ -1062,11 +1038,9 @@ int upload_mesh_impl(esdg_ctx *ctx, int N, int64_t K, const double *x, const dou
     B.part_cap = (n + T - 1) / T;
     TRY(alloc(ctx, &B.part, B.part_cap * 8 * sizeof(double)));
     TRY(alloc(ctx, &ctx->stage_d, 5 * n * sizeof(double)));
-    // zero-filled registers and traces
+    // zero-filled registers
     for (void *p : B.dU) CK(hipMemsetAsync(p, 0, n * r, ctx->stream));
-    CK(hipMemsetAsync(B.vtr, 0, K * 4 * nf * 4 * r, ctx->stream));
     for (void *p : B.eps) CK(hipMemsetAsync(p, 0, K * r, ctx->stream));
-    CK(hipMemsetAsync(B.count, 0, 4 * sizeof(int), ctx->stream));
     invalidate_eps(ctx);
     CK(hipMemsetAsync(B.dscal, 0, 8 * ni * sizeof(double), ctx->stream));
     CK(hipMemsetAsync(B.flags, 0, kNumFlags * sizeof(int), ctx->stream));
@@ -1401,7 +1375,7 @@ int esdg_autotune(esdg_ctx *ctx, int reps, int *choice, double ms[ESDG_STAGE_VAR
     const bool av = ctx->P.av_on != 0;
     const int base = ctx->cur, o1 = (base + 1) % 3;
     TRY(reset_flags(ctx));
-    if (av) TRY(launch_viscous(ctx, base, -1));
+    if (av) TRY(ensure_eps(ctx, base));
     // trial stages in the integrator's own form, W^n -> o1, each variant timed
     // over reps launches, twice, alternating: for LSRK(5,4) an interior stage
     // that reads the register dU (as stages 2-5 do) but does not write it --
@@ -1423,8 +1397,6 @@ int esdg_autotune(esdg_ctx *ctx, int reps, int *choice, double ms[ESDG_STAGE_VAR
             ctx->stage_variant = v;
             CK(hipEventRecord(e0, ctx->stream));
             for (int r = 0; r < reps; ++r) {
-                // the epilogue appends to o1's viscous-element list: empty it first
-                hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(64), 0, ctx->stream, ctx->B.count + o1, 0, 1);
                 StageCall sc = ssp ? StageCall{kModeSsp, av, base, o1, base, false, 0.0, 1.0, false, false, v}
                                    : StageCall{kModeLsrk, av, base, o1, base, false, kLsrkA[2], kLsrkB[2], false,
                                                false, v};
@@ -1484,7 +1456,17 @@ int esdg_step_stats(esdg_ctx *ctx, int64_t *limited, int64_t *viscous)
         if (ctx->P.av_on) {
             TRY(ensure_eps(ctx, ctx->cur));
             int cnt = 0;
-            CK(hipMemcpyAsync(&cnt, ctx->B.count + ctx->cur, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+            hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(64), 0, ctx->stream, ctx->B.count, 0, 1);
+            CK(hipGetLastError());
+            const unsigned g = (unsigned)((ctx->K + 255) / 256);
+            if (ctx->prec == 64)
+                hipLaunchKernelGGL(count_viscous_kernel<double>, dim3(g), dim3(256), 0, ctx->stream,
+                                   (const double *)ctx->B.eps[ctx->cur], ctx->B.count, ctx->K);
+            else
+                hipLaunchKernelGGL(count_viscous_kernel<float>, dim3(g), dim3(256), 0, ctx->stream,
+                                   (const float *)ctx->B.eps[ctx->cur], ctx->B.count, ctx->K);
+            CK(hipGetLastError());
+            CK(hipMemcpyAsync(&cnt, ctx->B.count, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
             CK(hipStreamSynchronize(ctx->stream));
             *viscous = cnt;
         }
@@ -1786,27 +1768,12 @@ int group_attempt(esdg_ctx *ctx, int base, bool first, int *hflags)
     } else {
         // a redo covers only the instances in the mask: the stage kernels
         // leave the other instances' elements, whose outputs of the step
-        // before are the same bit for bit, as they are.  Only the result's
-        // viscous-element list is rebuilt for all of them (each stage
-        // rebuilds its output's list from the elements it covers).
+        // before are the same bit for bit, as they are.
         ctx->cur = base;
         ctx->masked_attempt = ni > 1;
         const int st = launch_one_step(ctx, 0.0, false);
         ctx->masked_attempt = false;
         TRY(st);
-        if (ni > 1 && ctx->P.av_on) {
-            const int o = ctx->cur;
-            hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(64), 0, ctx->stream, ctx->B.count + o, 0, 1);
-            CK(hipGetLastError());
-            const unsigned g = (unsigned)((ctx->K + 255) / 256);
-            if (ctx->prec == 64)
-                hipLaunchKernelGGL(relist_kernel<double>, dim3(g), dim3(256), 0, ctx->stream,
-                                   (const double *)ctx->B.eps[o], ctx->B.list[o], ctx->B.count + o, ctx->K);
-            else
-                hipLaunchKernelGGL(relist_kernel<float>, dim3(g), dim3(256), 0, ctx->stream,
-                                   (const float *)ctx->B.eps[o], ctx->B.list[o], ctx->B.count + o, ctx->K);
-            CK(hipGetLastError());
-        }
     }
     TRY(dispatch(ctx, [&](auto L, auto r) {
         using R = decltype(r);
