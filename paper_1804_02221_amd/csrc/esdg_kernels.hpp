@@ -11,8 +11,8 @@
 //
 // Kernels: per RK stage stage_kernel (split-form volume term, interface flux,
 // source, artificial viscosity, stage update, positivity limiter and the
-// modal indicator of the result, fused); per step dt_kernel +
-// dt_finalize_kernel; indicator_kernel for a state no stage produced.
+// modal indicator of the result, fused); per step dt_kernel (adaptive steps);
+// indicator_kernel for a state no stage produced.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <cstdint>
@@ -1776,7 +1776,9 @@ __global__ __launch_bounds__(Shape<N>::T) void limit_kernel(Mesh<R> m, Phys<R> P
 // ------------------------------------------------------------------------
 // Time step bounds: CFL, viscous (AV), Lemma 2.  Minima go to 64 slots per
 // bound by atomicMin on the bit patterns of non-negative doubles (which order
-// like unsigned integers); dt_finalize_kernel reduces and resets them.
+// like unsigned integers); the workgroup that adds the last minima of an
+// instance reduces and resets its slots and sets its step (dt_finish), so
+// that a step's bounds are one launch.
 //
 // The last stage of every step leaves the per-element CFL and viscous bounds
 // of its output state in dtc/dtv (stage epilogue); the time-step pass then
@@ -1785,11 +1787,34 @@ __global__ __launch_bounds__(Shape<N>::T) void limit_kernel(Mesh<R> m, Phys<R> P
 // evaluates every bound itself.  All loops are flat over nodes, face nodes
 // and elements, with a fixed grid: each XCD takes one contiguous range of
 // each index space so that neighbour traces hit its L2.  Each workgroup
-// issues one atomic per bound.
+// issues one atomic per bound and one or two tickets.
 // ------------------------------------------------------------------------
 constexpr int kDtThreads = 256;
-constexpr int64_t kDtChunk = 256;   // elements per chunk of the ensemble time-step pass
 constexpr unsigned kDtMaxBlocks = 2048;
+constexpr int kDtUnroll = 4;        // face nodes a thread evaluates at once
+// Ticket counters of an instance: each workgroup counts in one of the first
+// kDtTickets, the last of each in the one behind them (a single counter would
+// serialise up to 2048 atomics on one address).
+constexpr int kDtTickets = 32;
+
+// One chunk of the ensemble time-step pass: elements [lo, hi) of instance
+// inst, its index among that instance's n chunks.
+struct DtChunk {
+    int64_t lo, hi;
+    int32_t inst, index, n, pad;
+};
+
+// A step exceeds the bounds of the state it produced when it is above this
+// many times the smaller of the CFL and viscous ones (the factors cfl and
+// cfl_visc are inside the bounds).
+constexpr double kStepBoundFactor = 2.0;
+
+// What the pass does with the minima: set each instance's step (and add it to
+// its time when advance), or check the step that produced the state against
+// them (a-posteriori check, reading of the remark that the step is adjusted
+// when a smaller one is found to be needed, section 6): raise kFlagStepBound,
+// and with iflags bit 2 of the instance's flag, and leave the step as it is.
+enum DtMode { kDtSet = 0, kDtAdvance = 1, kDtCheck = 2 };
 
 template <typename R>
 struct DtArgs {
@@ -1802,14 +1827,22 @@ struct DtArgs {
     const R *fgeo;             // [K][4][nf][3] outward unit normal and w_0 J / J^surf per face node
     const R *frec;             // with dtc: [K][4][nf][3] face records (h, u, v) of the state
     unsigned long long *slots; // [instance][3][kDtSlots]
-    const int64_t *cstart;     // ensembles: element chunks [cstart[c], cstart[c+1]) inside one instance
-    const int32_t *cinst;      //   and the instance of chunk c
+    const DtChunk *chunk;      // ensembles: [nchunks] element chunks, none across instances
     int64_t nchunks;
+    unsigned *tickets;         // [instance][kDtTickets + 1], zero between launches
+    double *dt;                // per instance k: dt[8k..8k+3] step and its bounds, dt[8k+4] time
+    int mode;                  // DtMode
+    int *flags, *iflags;
 };
 
 __device__ __forceinline__ void slot_min(unsigned long long *slot, double v)
 {
-    if (v >= 0.0 && v < __builtin_huge_val()) atomicMin(slot, (unsigned long long)__double_as_longlong(v));
+    if (v >= 0.0 && v < __builtin_huge_val()) {
+        // (the old value is waited for: the minimum has then reached the
+        // device's point of coherence, see dt_finish)
+        const unsigned long long old = atomicMin(slot, (unsigned long long)__double_as_longlong(v));
+        asm volatile("" ::"v"(old));
+    }
 }
 
 template <typename R>
@@ -1942,31 +1975,37 @@ __device__ __forceinline__ R lemma2_bound_rec(const DtArgs<R> &a, int64_t f)
     return lemma2_formula<R>(hm, hp, utm, utp, w0a, a.P);
 }
 
-// Minimum of the Lemma 2 bounds over the face nodes of range r.  Each
-// iteration takes U face nodes at once, with clamped indices and no branch,
+// Minimum of the Lemma 2 bounds over the face nodes b, b + stride, ... < e.
+// Each iteration takes U of them at once, with clamped indices and no branch,
 // so that the loads of all U (face map, then both traces) are in flight
 // together; the minimum does not depend on the order.
-template <int N, typename R, bool REC>
-__device__ __forceinline__ R lemma2_min(const DtArgs<R> &a, XcdRange r)
+template <int N, typename R, bool REC, int U>
+__device__ __forceinline__ R lemma2_min(const DtArgs<R> &a, int64_t b, int64_t e, int64_t stride)
 {
-    constexpr int U = 4;
     R posb = R(3.0e38);
-    for (; r.b < r.e; r.b += U * r.stride) {
+    for (; b < e; b += U * stride) {
         R v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t f = r.b + u * r.stride;
-            const int64_t fc = f < r.e ? f : r.e - 1;
+            const int64_t f = b + u * stride;
+            const int64_t fc = f < e ? f : e - 1;
             if constexpr (REC) v[u] = lemma2_bound_rec<N, R>(a, fc);
             else v[u] = lemma2_bound<N, R>(a, fc);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const bool in = r.b + u * r.stride < r.e;
+            const bool in = b + u * stride < e;
             posb = (in && v[u] < posb) ? v[u] : posb;
         }
     }
     return posb;
+}
+
+// After a step: from the face records its last stage left (with dtc).
+template <int N, typename R, int U>
+__device__ __forceinline__ R lemma2_min(const DtArgs<R> &a, int64_t b, int64_t e, int64_t stride)
+{
+    return a.frec ? lemma2_min<N, R, true, U>(a, b, e, stride) : lemma2_min<N, R, false, U>(a, b, e, stride);
 }
 
 // CFL bound at node q from the stored state and metric.
@@ -2003,6 +2042,84 @@ __device__ __forceinline__ void dt_block_min(R cflb, R viscb, R posb, unsigned l
     lds_sync<T>();
 }
 
+// Minimum over the wave of an instance's slots of one bound, which go back to
+// +inf.  The loads are atomic (past this XCD's L2).
+__device__ __forceinline__ double take_slots(unsigned long long *slots, int lane)
+{
+    static_assert(kDtSlots == 64, "one slot per lane");
+    const unsigned long long v = __hip_atomic_load(&slots[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    slots[lane] = 0x7FF0000000000000ull;
+    return wave_min(__longlong_as_double((long long)v));
+}
+
+// Called by every workgroup when its minima of instance k are in the slots:
+// the last of the n workgroups (or chunks), of which this is number idx, does
+// what a.mode asks with the minima.  A ticket a piece and no waiting: every
+// workgroup ends whatever the others do.  Slots and tickets are only touched
+// by device-scope atomics, and a workgroup draws its ticket when its own
+// minima's atomics have returned: whoever draws the last one finds them all.
+// (With fences instead, each a write-back of the XCD's L2, the pass took twice
+// its time on a large mesh.  As a launch of its own behind the pass this took
+// another 4.7 us a step.)
+template <typename R>
+__device__ __forceinline__ void dt_finish(const DtArgs<R> &a, int k, unsigned idx, unsigned n)
+{
+    __shared__ int s_last;
+    __shared__ double s_min[3];
+    const int t = threadIdx.x;
+    // (behind dt_block_min's last barrier its three lanes' atomics have returned)
+    if (t == 0) {
+        unsigned *const tk = a.tickets + (int64_t)k * (kDtTickets + 1);
+        // (few workgroups: one counter)
+        const unsigned sub = idx % kDtTickets, in_sub = (n - sub + kDtTickets - 1) / kDtTickets;
+        const bool two = n > (unsigned)kDtTickets;
+        bool up = !two;
+        if (two && atomicAdd(&tk[sub], 1u) == in_sub - 1) {
+            atomicExch(&tk[sub], 0u);
+            up = true;
+        }
+        int last = 0;
+        if (up && atomicAdd(&tk[kDtTickets], 1u) == (two ? (unsigned)kDtTickets : n) - 1) {
+            atomicExch(&tk[kDtTickets], 0u);
+            last = 1;
+        }
+        s_last = last;
+    }
+    __syncthreads();
+    if (s_last) {
+        unsigned long long *const sl = a.slots + (int64_t)k * 3 * kDtSlots;
+        const int w = t >> 6;
+        if (w < 3) {
+            const double v = take_slots(sl + w * kDtSlots, t & 63);
+            if ((t & 63) == 0) s_min[w] = v;
+        }
+        __syncthreads();
+        if (t == 0) {
+            double *const dt = a.dt + 8 * (int64_t)k;
+            const double cfl = s_min[0], visc = s_min[1], pos = s_min[2];
+            if (a.mode == kDtCheck) {
+                if (dt[0] > kStepBoundFactor * fmin(cfl, visc)) {
+                    atomicOr(&a.flags[kFlagStepBound], 1);
+                    if (a.iflags) atomicOr(&a.iflags[k], 2);
+                }
+            } else {
+                double step = fmin(cfl, visc);
+                if (a.P.limiter_on) step = fmin(step, pos);
+                if (!(step > 0.0) || !(step < __builtin_huge_val())) {
+                    atomicOr(&a.flags[kFlagDtPos], 1);
+                    step = 0.0;
+                }
+                dt[0] = step;
+                dt[1] = cfl;
+                dt[2] = visc;
+                dt[3] = pos;
+                if (a.mode == kDtAdvance) dt[4] += step;
+            }
+        }
+    }
+    __syncthreads();   // the next chunk's minima and tickets
+}
+
 template <int N, typename R>
 __global__ __launch_bounds__(kDtThreads) void dt_kernel(DtArgs<R> a)
 {
@@ -2034,12 +2151,12 @@ __global__ __launch_bounds__(kDtThreads) void dt_kernel(DtArgs<R> a)
             }
         }
     }
-    if (a.P.limiter_on) {
-        // after a step: the face records its last stage left (with dtc)
-        posb = a.frec ? lemma2_min<N, R, true>(a, XcdRange(K * 4 * nf, T))
-                      : lemma2_min<N, R, false>(a, XcdRange(K * 4 * nf, T));
+    if (a.P.limiter_on && a.mode != kDtCheck) {
+        const XcdRange r(K * 4 * nf, T);
+        posb = lemma2_min<N, R, kDtUnroll>(a, r.b, r.e, r.stride);
     }
     dt_block_min<R>(cflb, viscb, posb, a.slots, blockIdx.x % kDtSlots);
+    dt_finish<R>(a, 0, blockIdx.x, gridDim.x);
 }
 
 // The same per instance of an ensemble: each workgroup takes whole chunks
@@ -2051,7 +2168,8 @@ __global__ __launch_bounds__(kDtThreads) void dt_batch_kernel(DtArgs<R> a)
     constexpr int nf = N + 1, np = nf * nf, T = kDtThreads;
     const int t = threadIdx.x;
     for (int64_t c = blockIdx.x; c < a.nchunks; c += gridDim.x) {
-        const int64_t lo = a.cstart[c], hi = a.cstart[c + 1];
+        const DtChunk ch = a.chunk[c];
+        const int64_t lo = ch.lo, hi = ch.hi;
         R cflb = R(3.0e38), viscb = R(3.0e38), posb = R(3.0e38);
         if (a.dtc) {
             for (int64_t e = lo + t; e < hi; e += T) {
@@ -2077,13 +2195,10 @@ __global__ __launch_bounds__(kDtThreads) void dt_batch_kernel(DtArgs<R> a)
                 }
             }
         }
-        if (a.P.limiter_on) {
-            for (int64_t f = lo * 4 * nf + t; f < hi * 4 * nf; f += T) {
-                const R v = a.frec ? lemma2_bound_rec<N, R>(a, f) : lemma2_bound<N, R>(a, f);
-                posb = v < posb ? v : posb;
-            }
-        }
-        dt_block_min<R>(cflb, viscb, posb, a.slots + (int64_t)a.cinst[c] * 3 * kDtSlots, (int)(c % kDtSlots));
+        if (a.P.limiter_on && a.mode != kDtCheck)
+            posb = lemma2_min<N, R, 1>(a, lo * 4 * nf + t, hi * 4 * nf, T);
+        dt_block_min<R>(cflb, viscb, posb, a.slots + (int64_t)ch.inst * 3 * kDtSlots, ch.index % kDtSlots);
+        dt_finish<R>(a, ch.inst, (unsigned)ch.index, (unsigned)ch.n);
     }
 }
 

@@ -34,10 +34,10 @@ struct Bufs {
     int *count = nullptr;    // number of elements with eps > 0 (esdg_step_stats)
     double *dscal = nullptr; // per instance k: [8k..8k+3] dt and its bounds, [8k+4] time, [8k+5..7] spare
     unsigned long long *slots = nullptr;  // [instance][3][kDtSlots]
+    unsigned *tickets = nullptr;          // [instance][kDtTickets + 1]
     int n_inst = 1;          // instances (ensembles); > 1: the arrays below are set
     int32_t *inst = nullptr;    // [K] instance of each internal element
-    int64_t *cstart = nullptr;  // [nchunks + 1] element chunks of the time-step pass (never across instances)
-    int32_t *cinst = nullptr;   // [nchunks] instance of each chunk
+    void *chunk = nullptr;      // [nchunks] DtChunk: element chunks of the time-step pass (never across instances)
     int64_t nchunks = 0;
     int *flags = nullptr;    // status flags (kFlag* in esdg_kernels.hpp)
     int *iflags = nullptr;   // [n_inst] per-instance step flags (ensembles): 1 negative mean, 2 step above its result's bounds
@@ -83,7 +83,8 @@ struct Launch {
     static hipError_t stage(const Bufs &B, const StageCall &c, const Phys<R> &P, const Tab<R> &t,
                             hipStream_t s, Ev ev);
     static hipError_t limit(const Bufs &B, int buf, const Phys<R> &P, const Tab<R> &t, hipStream_t s);
-    static hipError_t dt(const Bufs &B, int in, bool av, bool fused, const Phys<R> &P, hipStream_t s, Ev ev);
+    static hipError_t dt(const Bufs &B, int in, bool av, bool fused, int mode, const Phys<R> &P, hipStream_t s,
+                         Ev ev);
     static hipError_t adjoint_stage(const Bufs &B, const AdjCall &c, const Phys<R> &P, const Tab<R> &t,
                                     hipStream_t s, Ev ev);
     static hipError_t bathymetry_adjoint(const Bufs &B, const Tab<double> &td, const double *gbx,

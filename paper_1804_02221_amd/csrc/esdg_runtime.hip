@@ -23,45 +23,15 @@ namespace esdg {
 constexpr int kProfStage = 0, kProfIndicator = 1, kProfAvFaces = 2, kProfAvDiv = 3, kProfDt = 4,
               kProfAdjoint = 5, kProfClasses = 6;
 
-// Reduce the dt slots: dt[0] = step, dt[1..3] = CFL, viscous, Lemma 2
-// bounds; fixed > 0 overrides the step.  Adds the step to *tacc when
-// advance.  Resets the slots to +inf.
-__global__ void dt_finalize_kernel(unsigned long long *slots_all, double *dt_all, double fixed, int use_pos,
-                                   int advance, int *flags)
+// Fixed step of the n instances (no bounds), added to their times.
+__global__ void fixed_step_kernel(double *dt_all, double fixed, int n)
 {
-    // workgroup k: instance k (slots [3][kDtSlots], scalars dt[8k..8k+7], time at dt[8k+4])
-    unsigned long long *slots = slots_all + (int64_t)blockIdx.x * 3 * kDtSlots;
-    double *dt = dt_all + 8 * (int64_t)blockIdx.x;
-    double *tacc = dt + 4;
-    __shared__ double s[3][kDtSlots];
-    const int t = threadIdx.x;
-    const unsigned long long inf = 0x7FF0000000000000ull;
-    for (int c = 0; c < 3; ++c) {
-        s[c][t] = __longlong_as_double((long long)slots[c * kDtSlots + t]);
-        slots[c * kDtSlots + t] = inf;
-    }
-    __syncthreads();
-    for (int st = kDtSlots / 2; st > 0; st >>= 1) {
-        if (t < st)
-            for (int c = 0; c < 3; ++c) s[c][t] = fmin(s[c][t], s[c][t + st]);
-        __syncthreads();
-    }
-    if (t == 0) {
-        double step = fixed;
-        if (!(fixed > 0.0)) {
-            step = fmin(s[0][0], s[1][0]);
-            if (use_pos) step = fmin(step, s[2][0]);
-            if (!(step > 0.0) || !(step < __builtin_huge_val())) {
-                atomicOr(&flags[kFlagDtPos], 1);
-                step = 0.0;
-            }
-        }
-        dt[0] = step;
-        dt[1] = s[0][0];
-        dt[2] = s[1][0];
-        dt[3] = s[2][0];
-        if (advance) tacc[0] += step;
-    }
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n) return;
+    double *dt = dt_all + 8 * (int64_t)k;
+    dt[0] = fixed;
+    dt[1] = dt[2] = dt[3] = __builtin_huge_val();
+    dt[4] += fixed;
 }
 
 __global__ void fill_u64_kernel(unsigned long long *p, unsigned long long v, int n)
@@ -93,37 +63,6 @@ __global__ void reset_flags_kernel(int *flags)
 {
     const int t = threadIdx.x;
     if (t < kNumFlags && t != kFlagBadJ) flags[t] = 0;
-}
-
-// A-posteriori check of a step (reading of the remark that the step is
-// adjusted when a smaller one is found to be needed, section 6): the dt pass
-// has just reduced the CFL and viscous bounds of the state the step produced
-// into the slots; a step above kStepBoundFactor times the smaller of the two
-// (the factors cfl and cfl_visc are inside the bounds) raises
-// kFlagStepBound.  Like dt_finalize_kernel it resets the slots; the step in
-// dt[0] is left as it was (a retry halves it).
-// One workgroup per instance (slots [instance][3][kDtSlots], step at
-// dt[8k]); with iflags (ensembles) the instance's flag gets bit 2.
-constexpr double kStepBoundFactor = 2.0;
-__global__ void step_check_kernel(unsigned long long *slots_all, double *dt_all, int *flags, int *iflags)
-{
-    __shared__ double s[2][kDtSlots];
-    unsigned long long *slots = slots_all + (int64_t)blockIdx.x * 3 * kDtSlots;
-    const double *dt = dt_all + 8 * (int64_t)blockIdx.x;
-    const int t = threadIdx.x;
-    const unsigned long long inf = 0x7FF0000000000000ull;
-    for (int c = 0; c < 2; ++c) s[c][t] = __longlong_as_double((long long)slots[c * kDtSlots + t]);
-    for (int c = 0; c < 3; ++c) slots[c * kDtSlots + t] = inf;
-    __syncthreads();
-    for (int st = kDtSlots / 2; st > 0; st >>= 1) {
-        if (t < st)
-            for (int c = 0; c < 2; ++c) s[c][t] = fmin(s[c][t], s[c][t + st]);
-        __syncthreads();
-    }
-    if (t == 0 && dt[0] > kStepBoundFactor * fmin(s[0][0], s[1][0])) {
-        atomicOr(&flags[kFlagStepBound], 1);
-        if (iflags) atomicOr(&iflags[blockIdx.x], 2);
-    }
 }
 
 // Ensemble retry support: step <- f * step for the instances k with mask[k],
@@ -435,7 +374,7 @@ void free_bufs(esdg_ctx *c)
     Bufs &B = c->B;
     void *ps[] = {B.x, B.y, B.xr, B.yr, B.mref, B.Ax, B.Cx, B.Ae, B.Ce, B.bx, B.by, B.bface, B.b, B.nbr, B.code, B.count,
                   B.gmax, B.dtc, B.dtv, B.fgeo, B.frec, B.tabg, B.dscal, B.slots, B.flags, B.part, c->stage_d,
-                  B.eps[0], B.eps[1], B.eps[2], B.vfl[0], B.vfl[1], B.vfl[2], B.inst, B.cstart, B.cinst,
+                  B.eps[0], B.eps[1], B.eps[2], B.vfl[0], B.vfl[1], B.vfl[2], B.inst, B.chunk, B.tickets,
                   B.iflags, B.imask};
     for (void *p : ps)
         if (p) (void)hipFree(p);
@@ -522,25 +461,41 @@ int launch_stage(esdg_ctx *ctx, StageCall sc)
     });
 }
 
-// Time step of state buffer buf (fixed > 0: that step) for every instance;
-// the bounds the last stage left for buf are used when current.
-int launch_dt(esdg_ctx *ctx, int buf, double fixed, int advance)
+// The bounds of state buffer buf for every instance (those the last stage left
+// for buf are used when current) and what mode does with them.
+int launch_dt(esdg_ctx *ctx, int buf, int mode)
 {
-    const bool av = ctx->P.av_on != 0;
-    if (!(fixed > 0.0)) {
-        const bool fused = ctx->dtb_buf == buf;
-        if (av && !fused) TRY(ensure_eps(ctx, buf));
-        TRY(timed(ctx, kProfDt, [&](Ev ev) {
-            return dispatch(ctx, [&](auto L, auto r) {
-                using R = decltype(r);
-                return decltype(L)::dt(ctx->B, buf, av, fused, phys<R>(ctx), ctx->stream, ev);
-            });
-        }));
-    }
-    hipLaunchKernelGGL(dt_finalize_kernel, dim3(n_inst(ctx)), dim3(kDtSlots), 0, ctx->stream, ctx->B.slots,
-                       ctx->B.dscal, fixed, ctx->P.limiter_on ? 1 : 0, advance, ctx->B.flags);
+    const bool av = ctx->P.av_on != 0, fused = ctx->dtb_buf == buf;
+    if (av && !fused) TRY(ensure_eps(ctx, buf));
+    return timed(ctx, kProfDt, [&](Ev ev) {
+        return dispatch(ctx, [&](auto L, auto r) {
+            using R = decltype(r);
+            return decltype(L)::dt(ctx->B, buf, av, fused, mode, phys<R>(ctx), ctx->stream, ev);
+        });
+    });
+}
+
+// The same fixed step for every instance.
+int launch_fixed_step(esdg_ctx *ctx, double dt)
+{
+    const int n = n_inst(ctx);
+    hipLaunchKernelGGL(fixed_step_kernel, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, ctx->stream, ctx->B.dscal, dt,
+                       n);
     CK(hipGetLastError());
     return ESDG_OK;
+}
+
+// Check of the step just taken against the bounds of its result: the last
+// stage left them, and they stay current for the next step's pass.
+int launch_step_check(esdg_ctx *ctx)
+{
+    return dispatch(ctx, [&](auto L, auto r) {
+               using R = decltype(r);
+               return decltype(L)::dt(ctx->B, ctx->cur, ctx->P.av_on != 0, true, kDtCheck, phys<R>(ctx), ctx->stream,
+                                      Ev{});
+           }) == hipSuccess
+               ? ESDG_OK
+               : fail(ctx, ESDG_EHIP, "launch of the step check failed");
 }
 
 int reset_flags(esdg_ctx *ctx)
@@ -656,7 +611,7 @@ int launch_one_step(esdg_ctx *ctx, double dt, bool with_dt = true)
     // restarts from it without a copy
     const int base = ctx->cur;
     const int o1 = (base + 1) % 3, o2 = (base + 2) % 3;
-    if (with_dt) TRY(launch_dt(ctx, base, dt > 0.0 ? dt : 0.0, 1));
+    if (with_dt) TRY(dt > 0.0 ? launch_fixed_step(ctx, dt) : launch_dt(ctx, base, kDtAdvance));
     int in = base;
     for (int k = 0; k < nst; ++k) {
         const int out = (k % 2 == 0) ? o1 : o2;
@@ -1006,27 +961,30 @@ int upload_mesh_impl(esdg_ctx *ctx, int N, int64_t K, const double *x, const dou
     TRY(alloc(ctx, &B.count, sizeof(int)));
     TRY(alloc(ctx, &B.dscal, 8 * ni * sizeof(double)));
     TRY(alloc(ctx, &B.slots, (size_t)3 * kDtSlots * ni * sizeof(unsigned long long)));
+    TRY(alloc(ctx, &B.tickets, (size_t)(kDtTickets + 1) * ni * sizeof(unsigned)));
+    CK(hipMemsetAsync(B.tickets, 0, (size_t)(kDtTickets + 1) * ni * sizeof(unsigned), ctx->stream));
     B.n_inst = ni;
     if (ni > 1) {
         // instance of every (internal) element and chunks of the time-step pass
-        std::vector<int64_t> cst;
-        std::vector<int32_t> cin;
-        for (int k = 0; k < ni; ++k)
-            for (int64_t e = off[k]; e < off[k + 1]; e += kDtChunk) {
-                cst.push_back(e);
-                cin.push_back(k);
-            }
-        cst.push_back(K);
-        B.nchunks = (int64_t)cin.size();
+        // (about 2048 chunks of at most 256 and at least 8 elements: fewer,
+        // larger ones left most of the chip idle and walked their face nodes
+        // one after the other, 20-33 us where 12 meshes of 16^2 to 64^2
+        // elements now take 13)
+        const int64_t per = std::max<int64_t>(8, std::min<int64_t>(256, K / kDtMaxBlocks));
+        std::vector<DtChunk> chunks;
+        for (int k = 0; k < ni; ++k) {
+            const int32_t n = (int32_t)((off[k + 1] - off[k] + per - 1) / per);
+            for (int32_t c = 0; c < n; ++c)
+                chunks.push_back(DtChunk{off[k] + c * per, std::min(off[k + 1], off[k] + (c + 1) * per), k, c, n, 0});
+        }
+        B.nchunks = (int64_t)chunks.size();
         TRY(alloc(ctx, &B.inst, K * sizeof(int32_t)));
         TRY(alloc(ctx, &B.iflags, ni * sizeof(int)));
         TRY(alloc(ctx, &B.imask, ni * sizeof(int)));
         CK(hipMemsetAsync(B.iflags, 0, ni * sizeof(int), ctx->stream));
-        TRY(alloc(ctx, &B.cstart, cst.size() * sizeof(int64_t)));
-        TRY(alloc(ctx, &B.cinst, cin.size() * sizeof(int32_t)));
+        TRY(alloc(ctx, &B.chunk, chunks.size() * sizeof(DtChunk)));
         CK(hipMemcpyAsync(B.inst, inst_of.data(), K * sizeof(int32_t), hipMemcpyHostToDevice, ctx->stream));
-        CK(hipMemcpyAsync(B.cstart, cst.data(), cst.size() * sizeof(int64_t), hipMemcpyHostToDevice, ctx->stream));
-        CK(hipMemcpyAsync(B.cinst, cin.data(), cin.size() * sizeof(int32_t), hipMemcpyHostToDevice, ctx->stream));
+        CK(hipMemcpyAsync(B.chunk, chunks.data(), chunks.size() * sizeof(DtChunk), hipMemcpyHostToDevice, ctx->stream));
         CK(hipStreamSynchronize(ctx->stream));
     }
     TRY(alloc(ctx, &B.flags, kNumFlags * sizeof(int)));
@@ -1178,7 +1136,7 @@ int esdg_compute_dt(esdg_ctx *ctx, double out[4])
     if (!out) return ctx ? fail(ctx, ESDG_EINVAL, "null pointer") : ESDG_EINVAL;
     if (!check_ctx(ctx, true)) return ESDG_EINVAL;
     TRY(reset_flags(ctx));
-    TRY(launch_dt(ctx, ctx->cur, 0.0, 0));
+    TRY(launch_dt(ctx, ctx->cur, kDtSet));
     CK(hipMemcpyAsync(out, ctx->B.dscal, 4 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
     CK(hipStreamSynchronize(ctx->stream));
     return ESDG_OK;
@@ -1208,18 +1166,7 @@ int esdg_step(esdg_ctx *ctx, int nsteps, double dt, double *t_out)
                 ctx->cur = base;
                 TRY(launch_one_step(ctx, dt, false));
             }
-            {
-                // check the step against the bounds of the state it produced (the
-                // last stage left them; the next step's dt pass recomputes them)
-                TRY(dispatch(ctx, [&](auto L, auto r) {
-                    using R = decltype(r);
-                    return decltype(L)::dt(ctx->B, ctx->cur, ctx->P.av_on != 0, true, phys<R>(ctx), ctx->stream,
-                                           Ev{});
-                }));
-                hipLaunchKernelGGL(step_check_kernel, dim3(1), dim3(kDtSlots), 0, ctx->stream, ctx->B.slots,
-                                   ctx->B.dscal, ctx->B.flags, (int *)nullptr);
-                CK(hipGetLastError());
-            }
+            TRY(launch_step_check(ctx));
             int flags[kNumFlags];
             TRY(read_flags(ctx, flags));
             if (flags[kFlagNonFinite]) break;   // reported below; halving the step cannot help
@@ -1775,13 +1722,7 @@ int group_attempt(esdg_ctx *ctx, int base, bool first, int *hflags)
         ctx->masked_attempt = false;
         TRY(st);
     }
-    TRY(dispatch(ctx, [&](auto L, auto r) {
-        using R = decltype(r);
-        return decltype(L)::dt(ctx->B, ctx->cur, ctx->P.av_on != 0, true, phys<R>(ctx), ctx->stream, Ev{});
-    }));
-    hipLaunchKernelGGL(step_check_kernel, dim3((unsigned)ni), dim3(kDtSlots), 0, ctx->stream, ctx->B.slots,
-                       ctx->B.dscal, ctx->B.flags, ctx->B.iflags);
-    CK(hipGetLastError());
+    TRY(launch_step_check(ctx));
     CK(hipMemcpyAsync(hflags, ctx->B.flags, kNumFlags * sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
     CK(hipMemcpyAsync(hflags + kNumFlags, ctx->B.iflags, ni * sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
     return ESDG_OK;
