@@ -86,17 +86,11 @@ hipError_t Launch<N, R>::geometry(const Bufs &B, const Tab<double> &td, hipStrea
 }
 
 template <int N, typename R>
-hipError_t Launch<N, R>::bathymetry(const Bufs &B, const double *b, const Tab<double> &td, hipStream_t s)
+hipError_t Launch<N, R>::bathymetry(const Bufs &B, const double *b, const int32_t *perm, const Tab<double> &td,
+                                    hipStream_t s)
 {
-    constexpr int np = (N + 1) * (N + 1);
-    const int64_t n = B.K * np;
-    const int bs = 256;
-    hipLaunchKernelGGL((bathymetry_kernel<N, R>), dim3((unsigned)((n + bs - 1) / bs)), dim3(bs), 0, s, B.K,
-                       B.x, B.y, b, (R *)B.bx, (R *)B.by, (R *)B.bface, td);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((convert_kernel<double, R>), dim3((unsigned)((n + bs - 1) / bs)), dim3(bs), 0, s, b,
-                       (R *)B.b, n);
+    hipLaunchKernelGGL((bathymetry_kernel<N, R>), tile_grid<N>(B.K), dim3(Shape<N>::T), 0, s, B.K, B.x, B.y, b, perm,
+                       (R *)B.bx, (R *)B.by, (R *)B.bface, (R *)B.b, ntiles_of<N>(B.K), td);
     return hipGetLastError();
 }
 
@@ -157,10 +151,11 @@ hipError_t Launch<N, R>::stage(const Bufs &B, const StageCall &c, const Phys<R> 
     a.h0 = (const R *)B.W[c.base][0];
     a.hu0 = (const R *)B.W[c.base][1];
     a.hv0 = (const R *)B.W[c.base][2];
-    void *const *o = c.out_rhs ? B.Rb : B.W[c.out];
+    void *const *o = c.out_rhs ? (c.rhs_perm ? c.rhs_out : B.Rb) : B.W[c.out];
     a.oh = (R *)o[0];
     a.ohu = (R *)o[1];
     a.ohv = (R *)o[2];
+    a.perm = c.rhs_perm;
     a.dh = (R *)B.dU[0];
     a.dhu = (R *)B.dU[1];
     a.dhv = (R *)B.dU[2];
@@ -273,6 +268,8 @@ hipError_t Launch<N, R>::adjoint_stage(const Bufs &B, const AdjCall &c, const Ph
         a.gbx = c.gbx;
         a.gby = c.gby;
         a.gbn = c.gbn;
+        a.accumulate = c.accumulate ? 1 : 0;
+        a.perm = c.perm;
         a.ca = c.ca;
         a.cb = c.cb;
         a.dt = c.dt;
@@ -288,18 +285,16 @@ hipError_t Launch<N, R>::adjoint_stage(const Bufs &B, const AdjCall &c, const Ph
 
 template <int N, typename R>
 hipError_t Launch<N, R>::bathymetry_adjoint(const Bufs &B, const Tab<double> &td, const double *gbx,
-                                            const double *gby, const double *gbn, double *gb, hipStream_t s)
+                                            const double *gby, const double *gbn, const int32_t *perm, double *gb,
+                                            hipStream_t s)
 {
     if constexpr (std::is_same<R, double>::value) {
-        constexpr int np = (N + 1) * (N + 1);
-        const int64_t n = B.K * np;
-        const int bs = 256;
-        hipLaunchKernelGGL((bathymetry_adjoint_kernel<N>), dim3((unsigned)((n + bs - 1) / bs)), dim3(bs), 0, s,
-                           B.K, (const double *)B.Ax, (const double *)B.Cx, (const double *)B.Ae,
-                           (const double *)B.Ce, gbx, gby, gbn, gb, td);
+        hipLaunchKernelGGL((bathymetry_adjoint_kernel<N>), tile_grid<N>(B.K), dim3(Shape<N>::T), 0, s, B.K,
+                           (const double *)B.Ax, (const double *)B.Cx, (const double *)B.Ae, (const double *)B.Ce,
+                           gbx, gby, gbn, perm, gb, ntiles_of<N>(B.K), td);
         return hipGetLastError();
     } else {
-        (void)B; (void)td; (void)gbx; (void)gby; (void)gbn; (void)gb; (void)s;
+        (void)B; (void)td; (void)gbx; (void)gby; (void)gbn; (void)perm; (void)gb; (void)s;
         return hipErrorNotSupported;
     }
 }

@@ -518,54 +518,74 @@ __global__ void geometry_kernel(int64_t K, const double *__restrict__ x, const d
     }
 }
 
-// Split-form bathymetry derivatives (eq. SourceDisc, read with D) and face
-// traces of b; metrics recomputed in float64 from the coordinates.
+// Split-form bathymetry derivatives (eq. SourceDisc, read with D), face traces
+// and nodal copy of the caller's bathymetry b, whose element perm[e] is
+// internal element e; metric terms in float64 from the coordinates.  A tile's
+// coordinates, b and the products of its metric terms with b are staged in
+// LDS: with every thread forming the metric terms of both its lines again
+// from global memory (4(N+1)^2 cached loads a line), behind a pass that
+// brought b into internal order and before one that copied it, the three took
+// 66 us at 128^2, N = 5; now 12.4 (N = 7, 512^2: 2370 -> 208).
 template <int N, typename R>
-__global__ void bathymetry_kernel(int64_t K, const double *__restrict__ x, const double *__restrict__ y,
-                                  const double *__restrict__ b, R *bx, R *by, R *bface,
-                                  Tab<double> tab)
+__global__ __launch_bounds__(Shape<N>::T) void bathymetry_kernel(int64_t K, const double *__restrict__ x,
+                                                                 const double *__restrict__ y,
+                                                                 const double *__restrict__ b,
+                                                                 const int32_t *__restrict__ perm, R *bx, R *by,
+                                                                 R *bface, R *bnode, int64_t ntiles,
+                                                                 Tab<double> tab)
 {
-    constexpr int nf = N + 1, np = nf * nf;
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= K * np) return;
-    const int64_t e = q / np;
-    const int p = (int)(q - e * np), i = p / nf, j = p - i * nf;
-    const double *xe = x + e * np, *ye = y + e * np, *be = b + e * np;
-    // metric terms at the line nodes are needed inside D(y_eta b) etc.
-    const double x0 = xe[0], y0 = ye[0];
-    auto met = [&](int a, int c, double &xxi, double &xeta, double &yxi, double &yeta) {
-        xxi = xeta = yxi = yeta = 0.0;
-        for (int m = 0; m < nf; ++m) {
-            xxi += tab.D[a * nf + m] * (xe[m * nf + c] - x0);
-            yxi += tab.D[a * nf + m] * (ye[m * nf + c] - y0);
-            xeta += tab.D[c * nf + m] * (xe[a * nf + m] - x0);
-            yeta += tab.D[c * nf + m] * (ye[a * nf + m] - y0);
-        }
-    };
+    using S = Shape<N>;
+    constexpr int nf = S::nf, np = S::np, E = S::E, T = S::T;
+    __shared__ double s_x[T], s_y[T], s_b[T], s_p[4][T], s_D[nf * nf];
+    const int64_t tile = xcd_tile(ntiles);
+    if (tile < 0) return;
+    const int t = threadIdx.x;
+    const bool lane = t < E * np;
+    const int el = lane ? t / np : E - 1, p = lane ? t - el * np : 0, i = p / nf, j = p - i * nf;
+    const int64_t e = tile * E + el;
+    const bool act = lane && e < K;
+    const int64_t q = act ? e * np + p : 0;
+    for (int c = t; c < nf * nf; c += T) s_D[c] = tab.D[c];
+    const int64_t q0 = act ? e * np : 0;
+    const double bn = act ? b[(int64_t)perm[e] * np + p] : 0.0;
+    s_x[t] = x[q] - x[q0];
+    s_y[t] = y[q] - y[q0];
+    lds_sync<T>();
+    const int base = el * np;
+    double xxi = 0, xeta = 0, yxi = 0, yeta = 0;
+    for (int m = 0; m < nf; ++m) {
+        const double di = s_D[i * nf + m], dj = s_D[j * nf + m];
+        xxi += di * s_x[base + m * nf + j];
+        yxi += di * s_y[base + m * nf + j];
+        xeta += dj * s_x[base + i * nf + m];
+        yeta += dj * s_y[base + i * nf + m];
+    }
+    s_b[t] = bn;
+    s_p[0][t] = yeta * bn;
+    s_p[1][t] = xeta * bn;
+    s_p[2][t] = yxi * bn;
+    s_p[3][t] = xxi * bn;
+    lds_sync<T>();
     double Db_xi = 0, Dyb_xi = 0, Dxb_xi = 0, Db_eta = 0, Dyb_eta = 0, Dxb_eta = 0;
     for (int m = 0; m < nf; ++m) {
-        double a0, a1, a2, a3;
-        const double dxi = tab.D[i * nf + m], deta = tab.D[j * nf + m];
-        met(m, j, a0, a1, a2, a3);   // node (m, j)
-        const double bm = be[m * nf + j];
-        Db_xi += dxi * bm;
-        Dyb_xi += dxi * (a3 * bm);   // y_eta b
-        Dxb_xi += dxi * (a1 * bm);   // x_eta b
-        met(i, m, a0, a1, a2, a3);   // node (i, m)
-        const double bn = be[i * nf + m];
-        Db_eta += deta * bn;
-        Dyb_eta += deta * (a2 * bn); // y_xi b
-        Dxb_eta += deta * (a0 * bn); // x_xi b
+        const double dxi = s_D[i * nf + m], deta = s_D[j * nf + m];
+        const int qi = base + m * nf + j, qe = base + i * nf + m;
+        Db_xi += dxi * s_b[qi];
+        Dyb_xi += dxi * s_p[0][qi];   // y_eta b
+        Dxb_xi += dxi * s_p[1][qi];   // x_eta b
+        Db_eta += deta * s_b[qe];
+        Dyb_eta += deta * s_p[2][qe]; // y_xi b
+        Dxb_eta += deta * s_p[3][qe]; // x_xi b
     }
-    double xxi, xeta, yxi, yeta;
-    met(i, j, xxi, xeta, yxi, yeta);
+    if (!act) return;
     bx[q] = (R)(yeta * Db_xi + Dyb_xi - yxi * Db_eta - Dyb_eta);
     by[q] = (R)(-xeta * Db_xi - Dxb_xi + xxi * Db_eta + Dxb_eta);
-    // face traces: thread of a face node writes every side the node is on
-    if (j == 0) bface[(e * 4 + 0) * nf + i] = (R)be[p];
-    if (i == N) bface[(e * 4 + 1) * nf + j] = (R)be[p];
-    if (j == N) bface[(e * 4 + 2) * nf + i] = (R)be[p];
-    if (i == 0) bface[(e * 4 + 3) * nf + j] = (R)be[p];
+    bnode[q] = (R)bn;
+    // face traces: the thread of a face node writes every side the node is on
+    if (j == 0) bface[(e * 4 + 0) * nf + i] = (R)bn;
+    if (i == N) bface[(e * 4 + 1) * nf + j] = (R)bn;
+    if (j == N) bface[(e * 4 + 2) * nf + i] = (R)bn;
+    if (i == 0) bface[(e * 4 + 3) * nf + j] = (R)bn;
 }
 
 // ------------------------------------------------------------------------
@@ -962,6 +982,7 @@ struct StageArgs {
     const R *h, *hu, *hv;        // stage input W
     const R *h0, *hu0, *hv0;     // SSP: W^n
     R *oh, *ohu, *ohv;           // output: R (rhs mode) or the new state
+    const int32_t *perm;         // rhs mode: the caller's element of each (nullptr: internal order)
     R *dh, *dhu, *dhv;           // LSRK register dU (in place)
     int store_du;                // 0 on the last LSRK stage: the next step's first stage does not read dU
     // artificial viscosity (nullptr eps: off)
@@ -1602,7 +1623,11 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
     const R R3 = (-L3 - hg * byv + Lv3) * iJ;
 
     if constexpr (MODE == kModeRhs) {
-        if (act) { (late.oh + q0)[tq] = R1; (late.ohu + q0)[tq] = R2; (late.ohv + q0)[tq] = R3; }
+        if (act) {
+            // in the caller's element order where perm gives it
+            const int64_t o = late.perm ? (int64_t)late.perm[e] * np + p : q0 + tq;
+            late.oh[o] = R1; late.ohu[o] = R2; late.ohv[o] = R3;
+        }
         return;
     } else {
         const R dt = (R)late.dt[late.inst ? 8 * (int64_t)late.inst[act ? e : e0] : 0];
@@ -2248,16 +2273,6 @@ __global__ __launch_bounds__(Shape<N>::T) void diag_kernel(Mesh<R> m, Phys<R> P,
         lds_sync<T>();
     }
     if (t < 8) part[blockIdx.x * 8 + t] = s[t][0];
-}
-
-// ------------------------------------------------------------------------
-// Precision conversion
-// ------------------------------------------------------------------------
-template <typename A, typename B>
-__global__ void convert_kernel(const A *__restrict__ src, B *__restrict__ dst, int64_t n)
-{
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q < n) dst[q] = (B)src[q];
 }
 
 }  // namespace esdg

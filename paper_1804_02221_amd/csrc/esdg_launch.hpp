@@ -61,6 +61,8 @@ struct StageCall {
     bool store_du;     // LSRK: write the register dU (not needed after the last stage)
     int variant;       // stage-kernel workgroup size: 0 default, 1 alternative
     bool masked = false;  // ensembles: only the elements of instances with imask set
+    const int32_t *rhs_perm = nullptr;   // with out_rhs: write rhs_out in the caller's element order instead of Rb
+    void *rhs_out[3] = {};
 };
 
 // One reverse stage of the discrete adjoint (float64 contexts only).
@@ -69,15 +71,18 @@ struct AdjCall {
     const void *a[3], *c[3];   // dL/dW_k and A_{k+1} dL/dd_{k+1} (nullptr: zero)
     void *ao[3], *co[3];       // dL/dW_{k-1} and A_k dL/dd_k (co nullptr: not written)
     const void *x[3], *y[3];   // added to ao and to co (nullptr: zero; y may alias co)
-    double *gbx, *gby, *gbn;   // bathymetry cotangents, accumulated
+    double *gbx, *gby, *gbn;   // bathymetry cotangents
     double ca, cb, dt;         // A_k, B_k and the step
     double sa = 1.0;           // scale of a in ao (SSPRK: beta_k)
+    bool accumulate = true;    // add to gbx, gby, gbn (else they are set)
+    const int32_t *perm = nullptr;  // ao in the caller's element order
 };
 
 template <int N, typename R>
 struct Launch {
     static hipError_t geometry(const Bufs &B, const Tab<double> &td, hipStream_t s);
-    static hipError_t bathymetry(const Bufs &B, const double *b, const Tab<double> &td, hipStream_t s);
+    static hipError_t bathymetry(const Bufs &B, const double *b, const int32_t *perm, const Tab<double> &td,
+                                 hipStream_t s);
     static hipError_t indicator(const Bufs &B, int buf, const Phys<R> &P, const Tab<R> &t, hipStream_t s,
                                 Ev ev);
     static hipError_t stage(const Bufs &B, const StageCall &c, const Phys<R> &P, const Tab<R> &t,
@@ -88,7 +93,8 @@ struct Launch {
     static hipError_t adjoint_stage(const Bufs &B, const AdjCall &c, const Phys<R> &P, const Tab<R> &t,
                                     hipStream_t s, Ev ev);
     static hipError_t bathymetry_adjoint(const Bufs &B, const Tab<double> &td, const double *gbx,
-                                         const double *gby, const double *gbn, double *gb, hipStream_t s);
+                                         const double *gby, const double *gbn, const int32_t *perm, double *gb,
+                                         hipStream_t s);
     static hipError_t diag(const Bufs &B, int buf, const Phys<R> &P, const Tab<R> &t, int64_t *nblocks,
                            hipStream_t s);
     static int threads();

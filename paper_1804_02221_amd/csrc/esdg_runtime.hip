@@ -10,6 +10,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "esdg.h"
@@ -95,26 +96,39 @@ __global__ void set_scalar_kernel(double *p, double v, int n)
     if (k < n) p[8 * k] = v;
 }
 
-// Element permutation between the caller's order and the internal
-// locality order: internal element e holds the caller's element perm[e].
-template <typename A, typename B>
-__global__ void gather_kernel(const A *__restrict__ src, B *__restrict__ dst, const int32_t *__restrict__ perm,
-                              int64_t K, int np)
+// F fields of NP values per element between the caller's element order and the
+// internal locality order (internal element e holds the caller's element
+// perm[e]), all in one launch: a launch per field cost small meshes more than
+// the copies (setting a state at 37^2, N = 4: 14.7 us, now 6.9).
+template <typename T, int F>
+struct Fields {
+    T *p[F];
+};
+
+template <int NP, typename A, typename B, int F>
+__global__ void gather_kernel(Fields<const A, F> src, Fields<B, F> dst, const int32_t *__restrict__ perm, int64_t K,
+                              double *time, int n_time)
 {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= K * np) return;
-    const int64_t e = q / np;
-    dst[q] = (B)src[(int64_t)perm[e] * np + (q - e * np)];
+    // (a new state: the n_time instances' times, kept at time[8k], start over)
+    if (time && q < n_time) time[8 * q] = 0.0;
+    if (q >= K * NP) return;
+    const int64_t e = (uint64_t)q / NP, o = (int64_t)perm[e] * NP + (q - e * NP);
+#pragma unroll
+    for (int f = 0; f < F; ++f) dst.p[f][q] = (B)src.p[f][o];
 }
 
-template <typename A, typename B>
-__global__ void scatter_kernel(const A *__restrict__ src, B *__restrict__ dst, const int32_t *__restrict__ perm,
-                               int64_t K, int np)
+// Elements [e0, e0 + K) only; the caller's first of them goes to the start of
+// the destination (the instances of an ensemble keep their ranges).
+template <int NP, typename A, int F>
+__global__ void scatter_kernel(Fields<const A, F> src, Fields<double, F> dst, const int32_t *__restrict__ perm,
+                               int64_t e0, int64_t K)
 {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= K * np) return;
-    const int64_t e = q / np;
-    dst[(int64_t)perm[e] * np + (q - e * np)] = (B)src[q];
+    if (q >= K * NP) return;
+    const int64_t e = (uint64_t)q / NP, o = ((int64_t)perm[e0 + e] - e0) * NP + (q - e * NP);
+#pragma unroll
+    for (int f = 0; f < F; ++f) dst.p[f][o] = (double)src.p[f][e0 * NP + q];
 }
 
 // Metric terms in the ABI's layout and order: x_xi, x_eta, y_xi, y_eta, J (float64).
@@ -255,7 +269,7 @@ struct esdg_ctx {
         int32_t *ug = nullptr;     // [nu] those elements, [nu + 1] offsets, [ng] gauges sorted by element
         double *gH = nullptr;      // [ng] scratch for esdg_gauge_values
         double *lam = nullptr;     // [4][3][n]: dL/dW (two buffers), dL/d(register) (two buffers)
-        double *gbf = nullptr;     // [4][n]: cotangents of b_x, b_y, face b; assembled dL/db
+        double *gbf = nullptr;     // [3][n]: cotangents of b_x, b_y, face b
         double *ckpt = nullptr;    // [ckpt_cap][3][n] states at the checkpoints
         int64_t ckpt_cap = 0;
         double *store = nullptr;   // [store_cap][3][n] stage inputs of one segment
@@ -512,46 +526,112 @@ int read_flags(esdg_ctx *ctx, int flags[kNumFlags])
     return ESDG_OK;
 }
 
-// Copy a float64 host/device array in the caller's element order into a
-// context array (compute precision, internal order); per = values per element.
-int upload_field(esdg_ctx *ctx, void *dst, const double *src, int64_t per, int mem)
+// Call f with the values per element as a compile-time constant: one
+// (per_element) or the degree's nodes.
+template <typename F>
+int with_np(const esdg_ctx *c, bool per_element, F &&f)
 {
-    const int64_t n = ctx->K * per;
-    const double *s = src;
-    if (!mem) {
-        CK(hipMemcpyAsync(ctx->stage_d, src, n * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
-        s = ctx->stage_d;
+    if (per_element) return f(std::integral_constant<int, 1>{});
+    switch (c->N) {
+    case 2: return f(std::integral_constant<int, 9>{});
+    case 3: return f(std::integral_constant<int, 16>{});
+    case 4: return f(std::integral_constant<int, 25>{});
+    case 5: return f(std::integral_constant<int, 36>{});
+    case 6: return f(std::integral_constant<int, 49>{});
+    case 7: return f(std::integral_constant<int, 64>{});
+    case 8: return f(std::integral_constant<int, 81>{});
+    default: return ESDG_EINVAL;
     }
-    const unsigned g = (unsigned)((n + 255) / 256);
-    if (ctx->prec == 64)
-        hipLaunchKernelGGL((gather_kernel<double, double>), dim3(g), dim3(256), 0, ctx->stream, s,
-                           (double *)dst, ctx->perm, ctx->K, (int)per);
-    else
-        hipLaunchKernelGGL((gather_kernel<double, float>), dim3(g), dim3(256), 0, ctx->stream, s,
-                           (float *)dst, ctx->perm, ctx->K, (int)per);
+}
+
+// Copy F float64 host/device nodal arrays in the caller's element order into
+// context arrays (compute precision, internal order); with reset_time every
+// instance's time starts over.
+template <int F>
+int upload_fields(esdg_ctx *ctx, void *const (&dst)[F], const double *const (&src)[F], int mem,
+                  bool reset_time = false)
+{
+    static_assert(F <= 5, "the float64 staging holds five fields");
+    const int64_t n = nodes(ctx);
+    Fields<const double, F> s;
+    for (int f = 0; f < F; ++f) {
+        s.p[f] = src[f];
+        if (!mem) {
+            s.p[f] = ctx->stage_d + f * n;
+            CK(hipMemcpyAsync(ctx->stage_d + f * n, src[f], n * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
+        }
+    }
+    const int nt = reset_time ? n_inst(ctx) : 0;
+    double *const time = reset_time ? ctx->B.dscal + 4 : nullptr;
+    const unsigned g = (unsigned)((std::max<int64_t>(n, nt) + 255) / 256);
+    TRY(with_np(ctx, false, [&](auto np) -> int {
+        constexpr int NP = decltype(np)::value;
+        if (ctx->prec == 64) {
+            Fields<double, F> d;
+            for (int f = 0; f < F; ++f) d.p[f] = (double *)dst[f];
+            hipLaunchKernelGGL((gather_kernel<NP, double, double, F>), dim3(g), dim3(256), 0, ctx->stream, s, d,
+                               ctx->perm, ctx->K, time, nt);
+        } else {
+            Fields<float, F> d;
+            for (int f = 0; f < F; ++f) d.p[f] = (float *)dst[f];
+            hipLaunchKernelGGL((gather_kernel<NP, double, float, F>), dim3(g), dim3(256), 0, ctx->stream, s, d,
+                               ctx->perm, ctx->K, time, nt);
+        }
+        return ESDG_OK;
+    }));
     CK(hipGetLastError());
     if (!mem) CK(hipStreamSynchronize(ctx->stream));
     return ESDG_OK;
 }
 
-// Copy a context array out into a float64 host/device array in the caller's order.
-int download_field(esdg_ctx *ctx, double *dst, const void *src, int64_t per, int mem)
+// Elements [e0, e0 + K) of F context arrays in the caller's order to float64
+// device arrays.
+template <int F>
+int scatter_fields(esdg_ctx *ctx, double *const (&dst)[F], const void *const (&src)[F], bool per_element, int64_t e0,
+                   int64_t K)
 {
-    const int64_t n = ctx->K * per;
-    double *d = mem ? dst : ctx->stage_d;
-    const unsigned g = (unsigned)((n + 255) / 256);
-    if (ctx->prec == 64)
-        hipLaunchKernelGGL((scatter_kernel<double, double>), dim3(g), dim3(256), 0, ctx->stream,
-                           (const double *)src, d, ctx->perm, ctx->K, (int)per);
-    else
-        hipLaunchKernelGGL((scatter_kernel<float, double>), dim3(g), dim3(256), 0, ctx->stream,
-                           (const float *)src, d, ctx->perm, ctx->K, (int)per);
-    CK(hipGetLastError());
-    if (!mem) {
-        CK(hipMemcpyAsync(dst, ctx->stage_d, n * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-        CK(hipStreamSynchronize(ctx->stream));
-    }
+    return with_np(ctx, per_element, [&](auto np) -> int {
+        constexpr int NP = decltype(np)::value;
+        Fields<double, F> d;
+        for (int f = 0; f < F; ++f) d.p[f] = dst[f];
+        const unsigned g = (unsigned)((K * NP + 255) / 256);
+        if (ctx->prec == 64) {
+            Fields<const double, F> s;
+            for (int f = 0; f < F; ++f) s.p[f] = (const double *)src[f];
+            hipLaunchKernelGGL((scatter_kernel<NP, double, F>), dim3(g), dim3(256), 0, ctx->stream, s, d, ctx->perm,
+                               e0, K);
+        } else {
+            Fields<const float, F> s;
+            for (int f = 0; f < F; ++f) s.p[f] = (const float *)src[f];
+            hipLaunchKernelGGL((scatter_kernel<NP, float, F>), dim3(g), dim3(256), 0, ctx->stream, s, d, ctx->perm,
+                               e0, K);
+        }
+        CK(hipGetLastError());
+        return ESDG_OK;
+    });
+}
+
+// The F arrays staged at stage_d (n values each) to host arrays.
+template <int F>
+int staged_to_host(esdg_ctx *ctx, double *const (&dst)[F], int64_t n)
+{
+    for (int f = 0; f < F; ++f)
+        CK(hipMemcpyAsync(dst[f], ctx->stage_d + f * n, n * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+    CK(hipStreamSynchronize(ctx->stream));
     return ESDG_OK;
+}
+
+// Copy F context arrays out into float64 host/device arrays in the caller's order.
+template <int F>
+int download_fields(esdg_ctx *ctx, double *const (&dst)[F], const void *const (&src)[F], bool per_element, int mem)
+{
+    static_assert(F <= 5, "the float64 staging holds five fields");
+    if (mem) return scatter_fields<F>(ctx, dst, src, per_element, 0, ctx->K);
+    const int64_t n = per_element ? ctx->K : nodes(ctx);
+    double *st[F];
+    for (int f = 0; f < F; ++f) st[f] = ctx->stage_d + f * n;
+    TRY(scatter_fields<F>(ctx, st, src, per_element, 0, ctx->K));
+    return staged_to_host<F>(ctx, dst, n);
 }
 
 // Locality order of the elements: recursive coordinate bisection of the
@@ -716,10 +796,16 @@ int graph_step(esdg_ctx *ctx, double dt)
     return ESDG_OK;
 }
 
-int run_rhs(esdg_ctx *ctx, int buf)
+// The right-hand side of state buffer buf, into Rb (internal order) or, float64
+// contexts, into out in the caller's element order.
+int run_rhs(esdg_ctx *ctx, int buf, double *const *out = nullptr)
 {
     if (ctx->P.av_on) TRY(ensure_eps(ctx, buf));
     StageCall sc{kModeRhs, ctx->P.av_on != 0, buf, buf, buf, true, 0.0, 0.0, false};
+    if (out) {
+        sc.rhs_perm = ctx->perm;
+        for (int c = 0; c < 3; ++c) sc.rhs_out[c] = out[c];
+    }
     return launch_stage(ctx, sc);
 }
 
@@ -1018,10 +1104,12 @@ int upload_mesh_impl(esdg_ctx *ctx, int N, int64_t K, const double *x, const dou
             sy = ctx->stage_d + n;
         }
         const unsigned g = (unsigned)((n + 255) / 256);
-        hipLaunchKernelGGL((gather_kernel<double, double>), dim3(g), dim3(256), 0, ctx->stream, sx, B.x,
-                           ctx->perm, K, (int)npn);
-        hipLaunchKernelGGL((gather_kernel<double, double>), dim3(g), dim3(256), 0, ctx->stream, sy, B.y,
-                           ctx->perm, K, (int)npn);
+        TRY(with_np(ctx, false, [&](auto np) -> int {
+            hipLaunchKernelGGL((gather_kernel<decltype(np)::value, double, double, 2>), dim3(g), dim3(256), 0,
+                               ctx->stream, (Fields<const double, 2>{{sx, sy}}), (Fields<double, 2>{{B.x, B.y}}),
+                               ctx->perm, K, (double *)nullptr, 0);
+            return ESDG_OK;
+        }));
         CK(hipGetLastError());
     }
     CK(dispatch(ctx, [&](auto L, auto) { return decltype(L)::geometry(ctx->B, ctx->td, ctx->stream); }));
@@ -1058,11 +1146,9 @@ int esdg_set_bathymetry(esdg_ctx *ctx, const double *b, int mem)
         CK(hipMemcpyAsync(ctx->stage_d, b, n * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
         src = ctx->stage_d;
     }
-    double *db = ctx->stage_d + n;   // internal order
-    hipLaunchKernelGGL((gather_kernel<double, double>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                       ctx->stream, src, db, ctx->perm, ctx->K, (ctx->N + 1) * (ctx->N + 1));
-    CK(hipGetLastError());
-    CK(dispatch(ctx, [&](auto L, auto) { return decltype(L)::bathymetry(ctx->B, db, ctx->td, ctx->stream); }));
+    CK(dispatch(ctx, [&](auto L, auto) {
+        return decltype(L)::bathymetry(ctx->B, src, ctx->perm, ctx->td, ctx->stream);
+    }));
     CK(hipStreamSynchronize(ctx->stream));
     ctx->have_b = true;
     ++ctx->b_version;
@@ -1074,15 +1160,8 @@ int esdg_set_state(esdg_ctx *ctx, const double *h, const double *hu, const doubl
     if (!ctx || !h || !hu || !hv) return ESDG_EINVAL;
     if (!ctx->have_mesh) return fail(ctx, ESDG_EINVAL, "upload_mesh first");
     CK(hipSetDevice(ctx->device));
-    const int64_t n = nodes(ctx);
     ctx->cur = 0;
-    const int64_t per = n / ctx->K;
-    TRY(upload_field(ctx, ctx->B.W[0][0], h, per, mem));
-    TRY(upload_field(ctx, ctx->B.W[0][1], hu, per, mem));
-    TRY(upload_field(ctx, ctx->B.W[0][2], hv, per, mem));
-    hipLaunchKernelGGL(set_scalar_kernel, dim3(1), dim3(64), 0, ctx->stream, ctx->B.dscal + 4, 0.0,
-                       n_inst(ctx));
-    CK(hipGetLastError());
+    TRY(upload_fields<3>(ctx, ctx->B.W[0], {h, hu, hv}, mem, true));
     invalidate_eps(ctx);
     ctx->have_state = true;
     return ESDG_OK;
@@ -1093,25 +1172,25 @@ int esdg_get_state(esdg_ctx *ctx, double *h, double *hu, double *hv, int mem)
     if (!ctx || !h || !hu || !hv) return ESDG_EINVAL;
     if (!ctx->have_state) return fail(ctx, ESDG_EINVAL, "no state");
     CK(hipSetDevice(ctx->device));
-    const int64_t n = nodes(ctx);
-    const int64_t per = n / ctx->K;
-    TRY(download_field(ctx, h, ctx->B.W[ctx->cur][0], per, mem));
-    TRY(download_field(ctx, hu, ctx->B.W[ctx->cur][1], per, mem));
-    TRY(download_field(ctx, hv, ctx->B.W[ctx->cur][2], per, mem));
-    return ESDG_OK;
+    void *const *W = ctx->B.W[ctx->cur];
+    return download_fields<3>(ctx, {h, hu, hv}, {W[0], W[1], W[2]}, false, mem);
 }
 
 int esdg_rhs(esdg_ctx *ctx, double *rh, double *rhu, double *rhv, int mem)
 {
     if (!rh || !rhu || !rhv) return ctx ? fail(ctx, ESDG_EINVAL, "null pointer") : ESDG_EINVAL;
     if (!check_ctx(ctx, true)) return ctx ? ESDG_EINVAL : ESDG_EINVAL;
+    if (ctx->prec == 64) {
+        // written in the caller's order by the stage kernel itself
+        const int64_t n = nodes(ctx);
+        double *out[3] = {rh, rhu, rhv};
+        if (!mem)
+            for (int c = 0; c < 3; ++c) out[c] = ctx->stage_d + c * n;
+        TRY(run_rhs(ctx, ctx->cur, out));
+        return mem ? ESDG_OK : staged_to_host<3>(ctx, {rh, rhu, rhv}, n);
+    }
     TRY(run_rhs(ctx, ctx->cur));
-    const int64_t n = nodes(ctx);
-    const int64_t per = n / ctx->K;
-    TRY(download_field(ctx, rh, ctx->B.Rb[0], per, mem));
-    TRY(download_field(ctx, rhu, ctx->B.Rb[1], per, mem));
-    TRY(download_field(ctx, rhv, ctx->B.Rb[2], per, mem));
-    return ESDG_OK;
+    return download_fields<3>(ctx, {rh, rhu, rhv}, {ctx->B.Rb[0], ctx->B.Rb[1], ctx->B.Rb[2]}, false, mem);
 }
 
 int esdg_limit(esdg_ctx *ctx, int64_t *n_limited)
@@ -1285,7 +1364,7 @@ int esdg_get_eps(esdg_ctx *ctx, double *eps, int mem)
         CK(hipMemsetAsync(ctx->B.eps[ctx->cur], 0, ctx->K * rsz(ctx), ctx->stream));
         ctx->eps_valid[ctx->cur] = false;
     }
-    return download_field(ctx, eps, ctx->B.eps[ctx->cur], 1, mem);
+    return download_fields<1>(ctx, {eps}, {ctx->B.eps[ctx->cur]}, true, mem);
 }
 
 int esdg_get_geometry(esdg_ctx *ctx, double *xxi, double *xeta, double *yxi, double *yeta, double *J,
@@ -1859,13 +1938,17 @@ int esdg_ensemble_get_state(esdg_ensemble *en, int id, double *h, double *hu, do
     const auto &I = en->inst[id];
     auto &G = en->groups[I.group];
     const int64_t npn = (int64_t)(G.N + 1) * (G.N + 1);
-    const int64_t n = nodes(G.ctx);
-    int st = esdg_get_state(G.ctx, G.scratch, G.scratch + n, G.scratch + 2 * n, 1);
-    if (st) return efail_ctx(en, G.ctx, st);
+    // only the instance's elements: bringing the whole union into order for
+    // every instance made reading all of them quadratic in their number
+    const int64_t n = I.K * npn;
     double *dst[3] = {h, hu, hv};
-    for (int c = 0; c < 3; ++c)
-        if (hipMemcpyAsync(dst[c], G.scratch + c * n + I.off * npn, I.K * npn * sizeof(double),
-                           mem ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, G.stream) != hipSuccess)
+    double *out[3];
+    for (int c = 0; c < 3; ++c) out[c] = mem ? dst[c] : G.scratch + c * n;
+    void *const *W = G.ctx->B.W[G.ctx->cur];
+    const int st = scatter_fields<3>(G.ctx, out, {W[0], W[1], W[2]}, false, I.off, I.K);
+    if (st) return efail_ctx(en, G.ctx, st);
+    for (int c = 0; c < 3 && !mem; ++c)
+        if (hipMemcpyAsync(dst[c], out[c], n * sizeof(double), hipMemcpyDeviceToHost, G.stream) != hipSuccess)
             return efail(en, ESDG_EHIP, "hipMemcpyAsync failed");
     if (hipStreamSynchronize(G.stream) != hipSuccess) return efail(en, ESDG_EHIP, "hipStreamSynchronize failed");
     return ESDG_OK;
@@ -2013,7 +2096,7 @@ int adj_fields(esdg_ctx *ctx)
     auto &A = ctx->adj;
     const int64_t n = nodes(ctx);
     if (!A.lam) TRY(alloc(ctx, &A.lam, 12 * n * sizeof(double)));
-    if (!A.gbf) TRY(alloc(ctx, &A.gbf, 4 * n * sizeof(double)));
+    if (!A.gbf) TRY(alloc(ctx, &A.gbf, 3 * n * sizeof(double)));
     if (!A.loss) TRY(alloc(ctx, &A.loss, sizeof(double)));
     return ESDG_OK;
 }
@@ -2071,12 +2154,13 @@ int adj_stage(esdg_ctx *ctx, const AdjCall &c)
     });
 }
 
-int adj_assemble_b(esdg_ctx *ctx)
+// dL/db from the accumulated cotangents, to a device array in the caller's order.
+int adj_assemble_b(esdg_ctx *ctx, double *gb)
 {
     const int64_t n = nodes(ctx);
     double *g = ctx->adj.gbf;
     CK(dispatch(ctx, [&](auto L, auto) {
-        return decltype(L)::bathymetry_adjoint(ctx->B, ctx->td, g, g + n, g + 2 * n, g + 3 * n, ctx->stream);
+        return decltype(L)::bathymetry_adjoint(ctx->B, ctx->td, g, g + n, g + 2 * n, ctx->perm, gb, ctx->stream);
     }));
     return ESDG_OK;
 }
@@ -2178,18 +2262,21 @@ int esdg_rhs_vjp(esdg_ctx *ctx, const double *lh, const double *lhu, const doubl
         return ctx ? fail(ctx, ESDG_EINVAL, "null pointer") : ESDG_EINVAL;
     if (!check_adjoint_ctx(ctx)) return ESDG_EINVAL;
     TRY(adj_fields(ctx));
-    const int64_t n = nodes(ctx), per = n / ctx->K;
-    double *L = ctx->adj.lam;   // [0..2] result, [6..8] input cotangent
-    TRY(upload_field(ctx, L + 6 * n, lh, per, mem));
-    TRY(upload_field(ctx, L + 7 * n, lhu, per, mem));
-    TRY(upload_field(ctx, L + 8 * n, lhv, per, mem));
-    TRY(fill(ctx, ctx->adj.gbf, 0.0, 3 * n));
+    const int64_t n = nodes(ctx);
+    double *L = ctx->adj.lam;   // [6..8] input cotangent
+    TRY(upload_fields<3>(ctx, {L + 6 * n, L + 7 * n, L + 8 * n}, {lh, lhu, lhv}, mem));
+    // the results go to the caller's arrays (host: to the staging) in its order
+    double *out[4] = {gh, ghu, ghv, gb};
+    if (!mem)
+        for (int k = 0; k < 4; ++k) out[k] = ctx->stage_d + k * n;
     AdjCall c{};
+    c.accumulate = false;
+    c.perm = ctx->perm;
     for (int k = 0; k < 3; ++k) {
         c.W[k] = ctx->B.W[ctx->cur][k];
         c.a[k] = nullptr;
         c.c[k] = L + (6 + k) * n;
-        c.ao[k] = L + k * n;
+        c.ao[k] = out[k];
         c.co[k] = nullptr;
     }
     c.gbx = ctx->adj.gbf;
@@ -2199,12 +2286,9 @@ int esdg_rhs_vjp(esdg_ctx *ctx, const double *lh, const double *lhu, const doubl
     c.cb = 0.0;
     c.dt = 1.0;
     TRY(adj_stage(ctx, c));
-    TRY(adj_assemble_b(ctx));
-    TRY(download_field(ctx, gh, L, per, mem));
-    TRY(download_field(ctx, ghu, L + n, per, mem));
-    TRY(download_field(ctx, ghv, L + 2 * n, per, mem));
-    TRY(download_field(ctx, gb, ctx->adj.gbf + 3 * n, per, mem));
-    if (mem) CK(hipStreamSynchronize(ctx->stream));
+    TRY(adj_assemble_b(ctx, out[3]));
+    if (!mem) return staged_to_host<4>(ctx, {gh, ghu, ghv, gb}, n);
+    CK(hipStreamSynchronize(ctx->stream));
     return ESDG_OK;
 }
 
@@ -2273,7 +2357,7 @@ int esdg_adjoint_backward(esdg_ctx *ctx, double seed, double *gb, double *gh0, d
     if (A.b_version != ctx->b_version) return fail(ctx, ESDG_EINVAL, "the bathymetry changed since the forward sweep");
     if (!same_params(A.P, ctx->P)) return fail(ctx, ESDG_EINVAL, "the parameters changed since the forward sweep");
     if (!std::isfinite(seed)) return fail(ctx, ESDG_EINVAL, "seed must be finite");
-    const int64_t n = nodes(ctx), per = n / ctx->K;
+    const int64_t n = nodes(ctx);
     const int np = (ctx->N + 1) * (ctx->N + 1);
     const bool ssp = ctx->P.integrator == 1;
     const int S = ssp ? 3 : 5;   // stages per step
@@ -2353,11 +2437,11 @@ int esdg_adjoint_backward(esdg_ctx *ctx, double seed, double *gb, double *gh0, d
             }
         }
     }
-    TRY(adj_assemble_b(ctx));
-    TRY(download_field(ctx, gb, A.gbf + 3 * n, per, mem));
-    if (gh0) TRY(download_field(ctx, gh0, lamA[pa], per, mem));
-    if (ghu0) TRY(download_field(ctx, ghu0, lamA[pa] + n, per, mem));
-    if (ghv0) TRY(download_field(ctx, ghv0, lamA[pa] + 2 * n, per, mem));
+    TRY(adj_assemble_b(ctx, mem ? gb : ctx->stage_d));
+    if (!mem) TRY(staged_to_host<1>(ctx, {gb}, n));
+    double *const g0[3] = {gh0, ghu0, ghv0};
+    for (int k = 0; k < 3; ++k)
+        if (g0[k]) TRY(download_fields<1>(ctx, {g0[k]}, {lamA[pa] + k * n}, false, mem));
     CK(hipStreamSynchronize(ctx->stream));
     return ESDG_OK;
 }
