@@ -56,6 +56,15 @@ __device__ __forceinline__ R sgn(R x)
     return x > R(0) ? R(1) : (x < R(0) ? R(-1) : R(0));
 }
 
+// sqrt(x) and 1/sqrt(x), both zero unless x > 0.
+template <typename R>
+__device__ __forceinline__ void sqrt_rcp_wet(R x, R &s, R &i)
+{
+    const bool wet = x > R(0);
+    sqrt_rcp(wet ? x : R(1), s, i);
+    if (!wet) s = i = R(0);
+}
+
 // Reverse mode of interface_flux: cotangent (z0, z1, z2) of (F0, F1, F2) in,
 // cotangents of both traces out (the wave speed c = sqrt(g h) is folded into
 // the height).
@@ -67,8 +76,9 @@ __device__ __forceinline__ void interface_flux_vjp(R hm, R um, R vm, R bm, R hp,
     const R g = P.g;
     const R utm = nx * um + ny * vm, vtm = nx * vm - ny * um;
     const R utp = nx * up + ny * vp, vtp = nx * vp - ny * up;
-    const R cm = sqrt(g * fmax(hm, R(0)));
-    const R cp = sqrt(g * fmax(hp, R(0)));
+    R cm, cp, icm, icp;   // wave speeds and their reciprocals (zero where dry)
+    sqrt_rcp_wet(g * hm, cm, icm);
+    sqrt_rcp_wet(g * hp, cp, icp);
     const R ah = R(0.5) * (hm + hp), au = R(0.5) * (utm + utp), av = R(0.5) * (vtm + vtp);
     const R ac = R(0.5) * (cm + cp);
     // cotangent in the face frame: F1 = nx f1 - ny f2, F2 = ny f1 + nx f2
@@ -119,8 +129,8 @@ __device__ __forceinline__ void interface_flux_vjp(R hm, R um, R vm, R bm, R hp,
     bhp += R(0.5) * bah + hp * bah2;
     butm += R(0.5) * bau; butp += R(0.5) * bau;
     bvtm += R(0.5) * bav; bvtp += R(0.5) * bav;
-    if (cm > R(0)) bhm += R(0.25) * bac * g / cm;
-    if (cp > R(0)) bhp += R(0.25) * bac * g / cp;
+    bhm += R(0.25) * bac * g * icm;
+    bhp += R(0.25) * bac * g * icp;
     // rotation: ut = nx u + ny v, vt = nx v - ny u
     gm.h = bhm; gm.u = nx * butm - ny * bvtm; gm.v = ny * butm + nx * bvtm; gm.b = bbm;
     gp.h = bhp; gp.u = nx * butp - ny * bvtp; gp.v = ny * butp + nx * bvtp; gp.b = bbp;
@@ -161,32 +171,35 @@ struct AdjFacePrefetch {
 template <int N>
 __device__ __forceinline__ void adj_prefetch_face(const AdjArgs &a, int f, int64_t e0, AdjFacePrefetch &pf)
 {
-    constexpr int nf = N + 1;
+    constexpr int nf = N + 1, np = nf * nf;
     if (f >= Shape<N>::NFACE) return;
-    const int fel = f / (4 * nf), s = (f / nf) & 3, k = f - (f / nf) * nf;
-    const int64_t fe = e0 + fel;
-    if (fe >= a.m.K) return;
-    int ns, kk;
-    int64_t en;
-    const int64_t qn = nbr_node<N>(a.m, fe, s, k, en, ns, kk);
-    pf.wall = is_wall(a.m, fe, s);
+    const int side = f / nf, fel = side / 4, k = f - side * nf;
+    if (e0 + fel >= a.m.K) return;
+    const int32_t en = (a.m.nbr + 4 * e0)[side];
+    const int c = (a.m.code + 4 * e0)[side];
+    pf.bo = (a.m.bface + e0 * 4 * nf)[f];
+    const int ns = c & 3, kk = (c & 4) ? N - k : k;
+    int i, j;
+    side_node<N>(ns, kk, i, j);
+    const uint64_t qn = (uint64_t)(uint32_t)en * np + (uint32_t)(i * nf + j);
+    pf.wall = (c & 8) != 0;
     pf.hn = a.h[qn]; pf.hun = a.hu[qn]; pf.hvn = a.hv[qn];
     if (!pf.wall) {
         pf.nAx = a.m.Ax[qn]; pf.nCx = a.m.Cx[qn]; pf.nAe = a.m.Ae[qn]; pf.nCe = a.m.Ce[qn];
         if (a.c[0]) { pf.c0 = a.c[0][qn]; pf.c1 = a.c[1][qn]; pf.c2 = a.c[2][qn]; }
         if (a.a[0]) { pf.a0 = a.a[0][qn]; pf.a1 = a.a[1][qn]; pf.a2 = a.a[2][qn]; }
     }
-    pf.bo = a.m.bface[(fe * 4 + s) * nf + k];
-    pf.bn = a.m.bface[(en * 4 + ns) * nf + kk];
+    pf.bn = a.m.bface[(uint64_t)(uint32_t)en * (4 * nf) + (uint32_t)(ns * nf + kk)];
 }
 
-// Register budget of four waves per SIMD (128 VGPRs, a few spilled) for
-// N >= 3: unbounded it takes 132-134 VGPRs and three waves; measured 2.5%
-// faster per launch at 128^2, N = 5, and 2.7% at 192^2, N = 3 (five waves
-// spill 36 VGPRs and run 40% slower).  N = 2, with two face slots per lane,
-// spills 20 VGPRs under that budget and runs 14% slower: no budget there
-// (with each slot's loads grouped ahead of its evaluation it runs 12%
-// faster than before, 40.8 against 46.4 us at 256^2).
+// Register budget of four waves per SIMD (128 VGPRs, none spilled) for N >= 3;
+// five waves spill 28 VGPRs and take 48.7 us where this takes 31.4 (reverse
+// stage at 128^2, N = 5).  N = 2, with two face slots per lane, takes 138
+// VGPRs and no budget: under that of four waves it spilled and ran 14% slower.
+// With scalar tile bases and unconditional loads, one reciprocal square root
+// for a length and its inverse instead of a root and divisions, and the late
+// arguments, operands and lane indices read or formed again instead of kept,
+// a reverse stage went from 36.9 us to 31.4.
 template <int N>
 struct AdjWaves {
     static constexpr int value = N == 2 ? 1 : 4;
@@ -211,27 +224,30 @@ __global__ __launch_bounds__(Shape<N>::T, AdjWaves<N>::value) void adjoint_stage
     const int el = lane ? t / np : E - 1, p = lane ? t - el * np : 0, i = p / nf, j = p - i * nf;
     const int64_t e0 = tile * E, e = e0 + el;
     const bool act = lane && (e < a.m.K);
-    const int64_t q = e * np + p;
+    // fields at their tile's start (a scalar) plus the lane's offset, as in
+    // the forward stage kernel
+    const int64_t q0 = e0 * np;
+    const uint32_t tq = act ? (uint32_t)t : 0u;
     const Phys<R> &P = a.P;
 
-    R h = 0, hu = 0, hv = 0, Ax = 0, Cx = 0, Ae = 0, Ce = 0, A0 = 0, A1 = 0, A2 = 0, l0 = 0, l1 = 0, l2 = 0;
-    if (act) {
-        h = a.h[q]; hu = a.hu[q]; hv = a.hv[q];
-        Ax = a.m.Ax[q]; Cx = a.m.Cx[q]; Ae = a.m.Ae[q]; Ce = a.m.Ce[q];
-        if (a.a[0]) { A0 = a.a[0][q]; A1 = a.a[1][q]; A2 = a.a[2][q]; }
-        if (a.c[0]) { l0 = a.c[0][q]; l1 = a.c[1][q]; l2 = a.c[2][q]; }
-    }
+    const R dz_t = a.tg->Dz[t < nf * nf ? t : 0];
+    const R h = (a.h + q0)[tq], hu = (a.hu + q0)[tq], hv = (a.hv + q0)[tq];
+    const R Ax = (a.m.Ax + q0)[tq], Cx = (a.m.Cx + q0)[tq], Ae = (a.m.Ae + q0)[tq], Ce = (a.m.Ce + q0)[tq];
+    R l0 = 0, l1 = 0, l2 = 0;
+    if (a.c[0]) { l0 = (a.c[0] + q0)[tq]; l1 = (a.c[1] + q0)[tq]; l2 = (a.c[2] + q0)[tq]; }
+    R A0 = 0, A1 = 0, A2 = 0;
+    if (a.a[0]) { A0 = (a.a[0] + q0)[tq]; A1 = (a.a[1] + q0)[tq]; A2 = (a.a[2] + q0)[tq]; }
     // one face slot per lane: its loads go out with the element's own (with
     // two per lane, at N = 2, holding both would spill; they load after the
     // staging as the slots are evaluated)
     constexpr int NS = (NF + T - 1) / T;
     AdjFacePrefetch pf0;
     if constexpr (NS == 1) adj_prefetch_face<N>(a, t, e0, pf0);
-    if (act) { l0 += a.cb * A0; l1 += a.cb * A1; l2 += a.cb * A2; }
+    l0 += a.cb * A0; l1 += a.cb * A1; l2 += a.cb * A2;
     const R ih = rcp_wet(h, P.h_tol);
     const R u = hu * ih, v = hv * ih;
     const R J = Ce * Ax - Cx * Ae;
-    const R iJ = act ? R(1) / J : R(0);
+    const R iJ = rcp_nr(J);
     const R m0 = -l0 * iJ, m1 = -l1 * iJ, m2 = -l2 * iJ;
     s_h[t] = h;
     s_q[t] = double2{hu, hv};
@@ -239,15 +255,15 @@ __global__ __launch_bounds__(Shape<N>::T, AdjWaves<N>::value) void adjoint_stage
     s_a[t] = double2{Ax, Cx};
     s_b[t] = double2{Ae, Ce};
     s_m[0][t] = m0; s_m[1][t] = m1; s_m[2][t] = m2;
-    for (int c = t; c < nf * nf; c += T) s_dz[c] = a.tg->Dz[c];
+    static_assert(nf * nf <= T, "one table entry per lane");
+    if (t < nf * nf) s_dz[t] = dz_t;
     lds_sync<T>();
 
     // ---- interface: own term w.r.t. the '-' trace, neighbour's term w.r.t. its '+' trace ----
     auto face_slot = [&](const int f, const AdjFacePrefetch &pfr) {
-        const int fel = f / (4 * nf), s = (f / nf) & 3, k = f - (f / nf) * nf;
-        const int64_t fe = e0 + fel;
+        const int side = f / nf, fel = side / 4, s = side & 3, k = f - side * nf;
         R gh = 0, gu = 0, gv = 0, gb = 0;
-        if (fe < a.m.K) {
+        if (e0 + fel < a.m.K) {
             int fi, fj;
             side_node<N>(s, k, fi, fj);
             const int lp = fel * np + fi * nf + fj;
@@ -255,8 +271,9 @@ __global__ __launch_bounds__(Shape<N>::T, AdjWaves<N>::value) void adjoint_stage
             const double2 dir = (s & 1) ? s_a[lp] : s_b[lp];
             const R sg = (s == 0 || s == 3) ? R(-1) : R(1);
             const R snx = sg * dir.x, sny = sg * dir.y;
-            const R js = sqrt(snx * snx + sny * sny);
-            const R nx = snx / js, ny = sny / js;
+            R js, ijs;
+            sqrt_rcp(snx * snx + sny * sny, js, ijs);
+            const R nx = snx * ijs, ny = sny * ijs;
             const bool wall = pfr.wall;
             // neighbour's trace and cotangent mu_n = -l_n / J_n (a wall: the
             // own trace, mirrored, and no neighbour term)
@@ -270,7 +287,7 @@ __global__ __launch_bounds__(Shape<N>::T, AdjWaves<N>::value) void adjoint_stage
                 const R nJ = pfr.nCe * pfr.nAx - pfr.nCx * pfr.nAe;
                 R nl0 = pfr.c0, nl1 = pfr.c1, nl2 = pfr.c2;
                 if (a.a[0]) { nl0 += a.cb * pfr.a0; nl1 += a.cb * pfr.a1; nl2 += a.cb * pfr.a2; }
-                const R inJ = R(1) / nJ;
+                const R inJ = rcp_nr(nJ);
                 nm0 = nl0 * inJ; nm1 = nl1 * inJ; nm2 = nl2 * inJ;
             }
             const R bo = pfr.bo;
@@ -350,44 +367,51 @@ __global__ __launch_bounds__(Shape<N>::T, AdjWaves<N>::value) void adjoint_stage
     }
     lds_sync<T>();   // face slots complete
 
+    // the arguments and the lane's place afresh from here on (see kernarg and
+    // fresh): kept across the volume sums they spilled
+    const AdjArgs &late = kernarg<AdjArgs>();
+    const int tl = fresh(threadIdx.x);
+    const int le = lane ? tl / np : E - 1, lp = lane ? tl - le * np : 0, li = lp / nf, lj = lp - li * nf;
+    const uint32_t ql = act ? (uint32_t)tl : 0u;
+    const R g = late.P.g;
+    const R bxv = (late.m.bx + q0)[ql], byv = (late.m.by + q0)[ql];
+    // the incoming cotangents again rather than kept
+    R B0 = 0, B1 = 0, B2 = 0, x0 = 0, x1 = 0, x2 = 0, b0 = 0, b1 = 0, b2 = 0;
+    if (late.a[0]) { B0 = (late.a[0] + q0)[ql]; B1 = (late.a[1] + q0)[ql]; B2 = (late.a[2] + q0)[ql]; }
+    if (late.x[0]) { x0 = (late.x[0] + q0)[ql]; x1 = (late.x[1] + q0)[ql]; x2 = (late.x[2] + q0)[ql]; }
+    if (late.accumulate) { b0 = (late.gbx + q0)[ql]; b1 = (late.gby + q0)[ql]; b2 = (late.gbn + q0)[ql]; }
     // face cotangents of this node (primitive velocities), summed over its sides
     R fh = 0, fu = 0, fv = 0, fb = 0;
     {
-        const int fb0 = el * 4 * nf;
+        const int fb0 = le * 4 * nf;
         auto side = [&](int f) { fh += s_fg[0][f]; fu += s_fg[1][f]; fv += s_fg[2][f]; fb += s_fg[3][f]; };
-        if (j == 0) side(fb0 + 0 * nf + i);
-        if (i == N) side(fb0 + 1 * nf + j);
-        if (j == N) side(fb0 + 2 * nf + i);
-        if (i == 0) side(fb0 + 3 * nf + j);
+        if (lj == 0) side(fb0 + 0 * nf + li);
+        if (li == N) side(fb0 + 1 * nf + lj);
+        if (lj == N) side(fb0 + 2 * nf + li);
+        if (li == 0) side(fb0 + 3 * nf + lj);
     }
     if (!act) return;
-    const R g = P.g;
-    const R bxv = a.m.bx[q], byv = a.m.by[q];
     // u = hu/h: d/dhu = 1/h, d/dh = -u/h (zero below the dry cut-off: ih = 0)
     const R gh = R(-0.25) * (u * P1 + v * P2) * ih + R(0.5) * g * Gh + fh - (u * fu + v * fv) * ih +
                  R(0.5) * g * (m1 * bxv + m2 * byv);
     const R ghu = R(0.5) * Tu + R(0.25) * P1 * ih + fu * ih;
     const R ghv = R(0.5) * Tv + R(0.25) * P2 * ih + fv * ih;
-    const R dt = a.dt;
-    R x0 = 0, x1 = 0, x2 = 0;
-    if (a.x[0]) { x0 = a.x[0][q]; x1 = a.x[1][q]; x2 = a.x[2][q]; }
-    const int64_t qo = a.perm ? (int64_t)a.perm[e] * np + p : q;
-    a.ao[0][qo] = a.sa * A0 + dt * gh + x0;
-    a.ao[1][qo] = a.sa * A1 + dt * ghu + x1;
-    a.ao[2][qo] = a.sa * A2 + dt * ghv + x2;
-    if (a.co[0]) {
+    const R dt = late.dt;
+    const int64_t qo = late.perm ? (int64_t)late.perm[e0 + le] * np + lp : q0 + ql;
+    late.ao[0][qo] = late.sa * B0 + dt * gh + x0;
+    late.ao[1][qo] = late.sa * B1 + dt * ghu + x1;
+    late.ao[2][qo] = late.sa * B2 + dt * ghv + x2;
+    if (late.co[0]) {
         R y0 = 0, y1 = 0, y2 = 0;
-        if (a.y[0]) { y0 = a.y[0][q]; y1 = a.y[1][q]; y2 = a.y[2][q]; }
-        a.co[0][q] = a.ca * l0 + y0;
-        a.co[1][q] = a.ca * l1 + y1;
-        a.co[2][q] = a.ca * l2 + y2;
+        if (late.y[0]) { y0 = (late.y[0] + q0)[ql]; y1 = (late.y[1] + q0)[ql]; y2 = (late.y[2] + q0)[ql]; }
+        (late.co[0] + q0)[ql] = late.ca * l0 + y0;
+        (late.co[1] + q0)[ql] = late.ca * l1 + y1;
+        (late.co[2] + q0)[ql] = late.ca * l2 + y2;
     }
     const R hs = R(0.5) * g * h * dt;
-    R b0 = 0, b1 = 0, b2 = 0;
-    if (a.accumulate) { b0 = a.gbx[q]; b1 = a.gby[q]; b2 = a.gbn[q]; }
-    a.gbx[q] = b0 + hs * m1;
-    a.gby[q] = b1 + hs * m2;
-    a.gbn[q] = b2 + dt * fb;
+    (late.gbx + q0)[ql] = b0 + hs * m1;
+    (late.gby + q0)[ql] = b1 + hs * m2;
+    (late.gbn + q0)[ql] = b2 + dt * fb;
 }
 
 // gb = (d(b_x, b_y)/db)^T (gbx, gby) + gbn for the split derivatives of
