@@ -39,11 +39,16 @@ struct Shape {
     static_assert(E * np <= T, "elements must fit the workgroup");
 };
 
-// The alternative workgroup size of the stage kernel: 256 threads where the
-// default is one wave, else 128.
+// Workgroup sizes of the stage kernel: the default one is Shape's, but 256
+// threads at N = 2, where a wave's seven elements have 84 face slots and every
+// wave of a one-wave tile takes a second round of them for 20 lanes (with 28
+// elements' 336 slots, two waves of four do: 128 -> 123 us at 601^2; 192
+// threads 128, 128 threads 125; both slots of a lane prefetched 127); the
+// alternative one is one wave at N = 2, 256 threads at N = 3 and 7, else 128.
 template <int N>
-struct AltThreads {
-    static constexpr int value = Shape<N>::T == 64 ? 256 : 128;
+struct StageThreads {
+    static constexpr int dflt = N == 2 ? 256 : Shape<N>::T;
+    static constexpr int alt = N == 2 ? 64 : (Shape<N>::T == 64 ? 256 : 128);
 };
 
 template <int N, int TT>
@@ -59,8 +64,8 @@ struct TileShape {
 // Compiled variants of the stage kernel, chosen at run time by the
 // autotuner (esdg_autotune); every variant does the same arithmetic per
 // element in the same order (results are bitwise the same):
-//   0  the default tile of Shape, its register budget and partner unroll;
-//   1  the alternative workgroup size (AltThreads), no register budget;
+//   0  the default tile, its register budget and partner unroll;
+//   1  the alternative workgroup size (StageThreads), no register budget;
 //   2  the default tile with one wave per SIMD less in its register budget
 //      (more registers);
 //   3  the default tile with the partner loops unrolled by two instead of
@@ -70,7 +75,9 @@ struct TileShape {
 //      columns (no more LDS; StageCfg::SWZ); unrolled by two (a full unroll
 //      of the padded rows spills 50-270 registers).
 // Default register budget in the FP64 update modes: six waves per SIMD at
-// N = 6 and 7, five otherwise; in the FP32 update modes eight (seven for
+// N = 5, 6 and 7 (at N = 5, 255^2, 86 us with five and 82 with six), five
+// otherwise (six spill on wet/dry tiles: N = 3, 200^2 bowl 26.0 -> 28.2 us; on
+// all at N = 2 and 8: 129 -> 135, 57 -> 66); in the FP32 update modes eight (seven for
 // variant 2, none for variant 1): left free, the compiler gave some FP32
 // variants 100-120 registers; no constraint in the right-hand-side mode.
 // Against an unroll by two the full one runs 2-3% faster at N = 6 and within
@@ -80,8 +87,8 @@ constexpr int kStageVariants = 5;
 template <int N, int V>
 struct StageCfg {
     static_assert(V >= 0 && V < kStageVariants, "stage variant");
-    static constexpr int T = V == 1 ? AltThreads<N>::value : Shape<N>::T;
-    static constexpr int base_waves = V == 1 ? 1 : ((N == 6 || N == 7) ? 6 : 5);
+    static constexpr int T = V == 1 ? StageThreads<N>::alt : StageThreads<N>::dflt;
+    static constexpr int base_waves = V == 1 ? 1 : ((N >= 5 && N <= 7) ? 6 : 5);
     static constexpr int waves = V == 2 ? base_waves - 1 : base_waves;
     static constexpr int VU = V >= 3 ? 2 : N + 1;
     // Variant 4 avoids the LDS bank conflicts of the eta-direction partner
@@ -336,8 +343,10 @@ __device__ __forceinline__ void sqrt_rcp(double x, double &s, double &i)
 }
 __device__ __forceinline__ void sqrt_rcp(float x, float &s, float &i)
 {
-    s = sqrtf(x);
-    i = rcp_nr(s);
+    const float y = __builtin_amdgcn_rsqf(x);
+    s = x * y;
+    s = fmaf(fmaf(-s, s, x), 0.5f * y, s);
+    i = fmaf(y, fmaf(-s, y, 1.0f), y);
 }
 
 template <typename R>
@@ -1294,10 +1303,9 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
     }
     // The face slots' neighbour traces and face bathymetry are loaded here,
     // with the element's own data, so that their latency is not paid a second
-    // time after the LDS staging; a lane holds NS slots (two at N = 2, where
-    // seven elements' 84 face nodes outnumber the 64 lanes).
-    // With more slots than lanes (N = 2) only the first slot is prefetched;
-    // the few lanes with a further slot load it when they evaluate it.
+    // time after the LDS staging.  With more slots than lanes (N = 2) only
+    // the first slot is prefetched; the lanes with a further slot load it
+    // when they evaluate it.
     constexpr int NS = (NF + T - 1) / T;
     FacePrefetch<R> pf0;
     // (a one-trip loop here costs a VGPR and a dozen spilled SGPRs at N = 7)
@@ -1427,59 +1435,53 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
     R A1 = 0, A2 = 0, A3 = 0, C2 = 0, C3 = 0;
     if constexpr (kJumpForm<R>) {
         // single precision: the same sums taken over the partners' jumps
-        // from the own node (dX = X_m - X, t = 2 x own metric pair).  With
-        // F1'(own) = 4 (hu A + hv C) and F2'(own) the own momentum part,
-        //   F1'_m - F1'(own) = s_hu dA + s_hv dC + tA dhu + tC dhv
-        //   F2'_m - F2'(own) = 2u (F1'_m - F1'(own)) + du F1'_m + 2g h (h_m dA + tA dh)
+        // from the own node, dX = X_m - X.  With F1'(own) = 4 (hu A + hv C),
+        // F2'(own) the own momentum part and e = dhu sA + dhv sC,
+        //   F1'_m - F1'(own) = 2 (hu dA + hv dC) + e,  F1'_m = 2 (hu sA + hv sC) + e
+        //   F2'_m - F2'(own) = 2u (F1'_m - F1'(own)) + du F1'_m + 2g h (h dA + dh sA)
         // (F3' alike), so sum_m D (F' - F'(own)) holds no term of the size of
         // the flux itself; the row-sum parts D~ 1 F'(own) left out are the
-        // own-flux parts the face slots subtract (interface_flux_delta).
+        // own-flux parts the face slots subtract (interface_flux_delta).  The
+        // sums of D dA and D dC over both directions are the discrete metric
+        // identities (D_xi y_eta = D_eta y_xi, the terms being D's own
+        // derivatives of the coordinates): zero, left out, and with them the
+        // rounding of the stored terms that they would add.  18 operations a
+        // partner; with the jumps of A and C and those sums kept it was 27,
+        // and this kernel is
+        // bound by vector instructions: N = 7, 384^2 185 -> 174 us, N = 8,
+        // 150^2 42.5 -> 38.5.
         const int base = el * PS;
         constexpr int VU = StageCfg<N, V>::VU;
         // (the staged and own terms are relative to the element's middle
-        // node: the jumps from the own relative terms, t from the absolute
-        // ones, the sums from the own plus twice the reference)
+        // node: the sums of two absolute ones from the own plus twice the
+        // reference)
         const R *const mr = s_mref + 4 * el;
+        const R hu2 = R(2) * hu, hv2 = R(2) * hv;
+        auto pair = [&](R d, V2 am, V2 qm, V2 wm, R hm, R pA, R pC) {
+            const R sA = pA + am.x, sC = pC + am.y;
+            const R e = (qm.x - hu) * sA + (qm.y - hv) * sC;
+            const R dF = d * (hu2 * sA + hv2 * sC + e);
+            const R dh = d * (hm - h);
+            A1 += d * e;
+            A2 += dF * (wm.x - u);
+            A3 += dF * (wm.y - v);
+            C2 += dh * sA;
+            C3 += dh * sC;
+        };
         {
-            const R tA = R(2) * (Ax + mr[0]), tC = R(2) * (Cx + mr[1]);
             const R pA = Ax + R(2) * mr[0], pC = Cx + R(2) * mr[1];
 #pragma unroll VU
             for (int mm = 0; mm < nf; ++mm) {
                 const int qq = base + mm * RS + stage_col<N, V>(mm, j);
-                const R d = s_dz[i * nf + mm];
-                const V2 am = s_a[qq], qm = s_q[qq], wm = s_w[qq];
-                const R hm = s_h[qq];
-                const R dA = am.x - Ax, dC = am.y - Cx, dh = hm - h;
-                const R s1 = hu + qm.x, s2 = hv + qm.y;
-                const R F1 = s1 * (pA + am.x) + s2 * (pC + am.y);
-                const R dF1 = s1 * dA + s2 * dC + tA * (qm.x - hu) + tC * (qm.y - hv);
-                const R dF = d * F1;
-                A1 += d * dF1;
-                A2 += dF * (wm.x - u);
-                A3 += dF * (wm.y - v);
-                C2 += d * (hm * dA + tA * dh);
-                C3 += d * (hm * dC + tC * dh);
+                pair(s_dz[i * nf + mm], s_a[qq], s_q[qq], s_w[qq], s_h[qq], pA, pC);
             }
         }
         {
-            const R tA = R(2) * (Ae + mr[2]), tC = R(2) * (Ce + mr[3]);
             const R pA = Ae + R(2) * mr[2], pC = Ce + R(2) * mr[3];
 #pragma unroll VU
             for (int mm = 0; mm < nf; ++mm) {
                 const int qq = base + i * RS + stage_col<N, V>(i, mm);
-                const R d = s_dz[j * nf + mm];
-                const V2 bm = s_b[qq], qm = s_q[qq], wm = s_w[qq];
-                const R hm = s_h[qq];
-                const R dA = bm.x - Ae, dC = bm.y - Ce, dh = hm - h;
-                const R s1 = hu + qm.x, s2 = hv + qm.y;
-                const R F1 = s1 * (pA + bm.x) + s2 * (pC + bm.y);
-                const R dF1 = s1 * dA + s2 * dC + tA * (qm.x - hu) + tC * (qm.y - hv);
-                const R dF = d * F1;
-                A1 += d * dF1;
-                A2 += dF * (wm.x - u);
-                A3 += dF * (wm.y - v);
-                C2 += d * (hm * dA + tA * dh);
-                C3 += d * (hm * dC + tC * dh);
+                pair(s_dz[j * nf + mm], s_b[qq], s_q[qq], s_w[qq], s_h[qq], pA, pC);
             }
         }
     } else {
@@ -1531,10 +1533,15 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
     lds_sync<T>();   // face slots complete; staging region free from here on
     {
         const int fb = el * 4 * nf;
-        if (j == 0) { L1 += s_fl[0][fb + 0 * nf + i]; L2 += s_fl[1][fb + 0 * nf + i]; L3 += s_fl[2][fb + 0 * nf + i]; }
-        if (i == N) { L1 += s_fl[0][fb + 1 * nf + j]; L2 += s_fl[1][fb + 1 * nf + j]; L3 += s_fl[2][fb + 1 * nf + j]; }
-        if (j == N) { L1 += s_fl[0][fb + 2 * nf + i]; L2 += s_fl[1][fb + 2 * nf + i]; L3 += s_fl[2][fb + 2 * nf + i]; }
-        if (i == 0) { L1 += s_fl[0][fb + 3 * nf + j]; L2 += s_fl[1][fb + 3 * nf + j]; L3 += s_fl[2][fb + 3 * nf + j]; }
+        // (a node lies on at most one side of each direction)
+        if (j == 0 || j == N) {
+            const int f = fb + (j == 0 ? 0 : 2) * nf + i;
+            L1 += s_fl[0][f]; L2 += s_fl[1][f]; L3 += s_fl[2][f];
+        }
+        if (i == 0 || i == N) {
+            const int f = fb + (i == 0 ? 3 : 1) * nf + j;
+            L1 += s_fl[0][f]; L2 += s_fl[1][f]; L3 += s_fl[2][f];
+        }
     }
     if constexpr (kMetricRel<R>) {
         // the own terms absolute from here on
