@@ -191,8 +191,8 @@ hipError_t Launch<N, R>::limit(const Bufs &B, int buf, const Phys<R> &P, const T
 }
 
 template <int N, typename R>
-hipError_t Launch<N, R>::dt(const Bufs &B, int in, bool av, bool fused, int mode, const Phys<R> &P, hipStream_t s,
-                            Ev ev)
+hipError_t Launch<N, R>::dt(const Bufs &B, int in, bool av, bool fused, int mode, HostStatus *host,
+                            const Phys<R> &P, hipStream_t s, Ev ev)
 {
     DtArgs<R> a;
     a.m = mesh_view<R>(B);
@@ -214,6 +214,7 @@ hipError_t Launch<N, R>::dt(const Bufs &B, int in, bool av, bool fused, int mode
     a.mode = mode;
     a.flags = B.flags;
     a.iflags = B.iflags;
+    a.host = host;
     if (B.n_inst > 1) {
         const unsigned grid = (unsigned)(B.nchunks < (int64_t)kDtMaxBlocks ? B.nchunks : (int64_t)kDtMaxBlocks);
         launch_ev(dt_batch_kernel<N, R>, dim3(grid), dim3(kDtThreads), s, ev, a);

@@ -68,8 +68,7 @@ struct TileShape {
 //   1  the alternative workgroup size (StageThreads), no register budget;
 //   2  the default tile with one wave per SIMD less in its register budget
 //      (more registers);
-//   3  the default tile with the partner loops unrolled by two instead of
-//      fully;
+//   3  the default tile with the partner loops unrolled by two;
 //   4  the default tile with bank-conflict-free staging rows: padded by one
 //      node (the paper's LDS padding, appendix C), or at N = 7 XOR-swizzled
 //      columns (no more LDS; StageCfg::SWZ); unrolled by two (a full unroll
@@ -90,7 +89,10 @@ struct StageCfg {
     static constexpr int T = V == 1 ? StageThreads<N>::alt : StageThreads<N>::dflt;
     static constexpr int base_waves = V == 1 ? 1 : ((N >= 5 && N <= 7) ? 6 : 5);
     static constexpr int waves = V == 2 ? base_waves - 1 : base_waves;
-    static constexpr int VU = V >= 3 ? 2 : N + 1;
+    // partner-loop unroll, double and single precision: at N = 7 the doubles'
+    // by two (a smooth flow even; with wet/dry tiles at 128^2 40.4 -> 39.6 us,
+    // fewer registers being spilled on them)
+    static constexpr int VU = (V >= 3 || N == 7) ? 2 : N + 1, VU32 = V >= 3 ? 2 : N + 1;
     // Variant 4 avoids the LDS bank conflicts of the eta-direction partner
     // reads (a wave reads column mm of every row, rows 16(N+1) bytes apart in
     // FP64: at N = 7 eight rows on two bank groups).  At N = 7 the columns of
@@ -1105,6 +1107,13 @@ __device__ __forceinline__ void nbr_viscous_flux(const StageArgs<R> &a, int64_t 
     const R *const r = a.vfl + ((e * 4 + s) * nf + k) * 2;
     fu = r[0];
     fv = r[1];
+    // a corner also lies on a side t of the other direction (any other node:
+    // the same loads on side s, left out below, so that no branch holds them up)
+    const int t = (s & 1) ? (j == N ? 2 : (j == 0 ? 0 : -1)) : (i == N ? 1 : (i == 0 ? 3 : -1));
+    int64_t ec;
+    int nc, kc;
+    const int64_t qc = nbr_node<N>(a.m, e, t >= 0 ? t : s, t >= 0 ? ((s & 1) ? i : j) : k, ec, nc, kc);
+    const R hc = a.h[qc], huc = a.hu[qc], hvc = a.hv[qc];
     const int64_t q = e * np + i * nf + j;
     R Ax, Cx, Ae, Ce;
     metric_at(a.m, q, e, Ax, Cx, Ae, Ce);
@@ -1116,14 +1125,11 @@ __device__ __forceinline__ void nbr_viscous_flux(const StageArgs<R> &a, int64_t 
     const R d = (s & 1) ? aa : ee;
     fu += d * R(0.5) * (uo - u);
     fv += d * R(0.5) * (vo - v);
-    // a corner also lies on a side of the other direction
-    const int t = (s & 1) ? (j == N ? 2 : (j == 0 ? 0 : -1)) : (i == N ? 1 : (i == 0 ? 3 : -1));
     if (t >= 0) {
-        R ju, jv;
-        side_jump<N>(a, e, t, (s & 1) ? i : j, u, v, ju, jv);
+        const R ic = rcp_wet(hc, a.P.h_tol);
         const bool pos = ((s == 1 || s == 2) == (t == 1 || t == 2));
-        fu += (pos ? ae : -ae) * ju;
-        fv += (pos ? ae : -ae) * jv;
+        fu += (pos ? ae : -ae) * (R(0.5) * (huc * ic - u));
+        fv += (pos ? ae : -ae) * (R(0.5) * (hvc * ic - v));
     }
 }
 
@@ -1451,7 +1457,7 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
         // bound by vector instructions: N = 7, 384^2 185 -> 174 us, N = 8,
         // 150^2 42.5 -> 38.5.
         const int base = el * PS;
-        constexpr int VU = StageCfg<N, V>::VU;
+        constexpr int VU = StageCfg<N, V>::VU32;
         // (the staged and own terms are relative to the element's middle
         // node: the sums of two absolute ones from the own plus twice the
         // reference)
@@ -1577,20 +1583,18 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
         V2 fa = V2{R(0), R(0)}, fb = fa;
         if (visc) {
             const R eps_e = (late.eps + e0)[el];
+            // (the jumps' loads, two behind each other, go out ahead of the sums)
+            const R sx = i == N ? late.tab.iw0 : -late.tab.iw0, se = j == N ? late.tab.iw0 : -late.tab.iw0;
+            R jxu = 0, jxv = 0, jeu = 0, jev = 0;
+            if (i == 0 || i == N) side_jump<N>(late, e, i == N ? 1 : 3, j, u, v, jxu, jxv);
+            if (j == 0 || j == N) side_jump<N>(late, e, j == N ? 2 : 0, i, u, v, jeu, jev);
             R dxu, dxv, deu, dev;
             line_derivatives<N, R>(s_dz, i, j, [&](int r, int c) { return s_w[base + r * RS + stage_col<N, V>(r, c)]; },
                                    V2{u, v}, dxu, dxv, deu, dev);
-            const R iw = late.tab.iw0;
-            auto lift = [&](int s, int k, R &du, R &dv, R sg) {
-                R ju, jv;
-                side_jump<N>(late, e, s, k, u, v, ju, jv);
-                du += sg * ju;
-                dv += sg * jv;
-            };
-            if (i == N) lift(1, j, dxu, dxv, iw);
-            if (i == 0) lift(3, j, dxu, dxv, -iw);
-            if (j == N) lift(2, i, deu, dev, iw);
-            if (j == 0) lift(0, i, deu, dev, -iw);
+            dxu += sx * jxu;
+            dxv += sx * jxv;
+            deu += se * jeu;
+            dev += se * jev;
             // contravariant fluxes J grad(xi) . (h eps grad), J grad(eta) . (...)
             const R sc = h * eps_e / J;
             const R aa = sc * (Ax * Ax + Cx * Cx), ae = sc * (Ax * Ae + Cx * Ce), ee = sc * (Ae * Ae + Ce * Ce);
@@ -1836,6 +1840,22 @@ struct DtChunk {
     int32_t inst, index, n, pad;
 };
 
+// Step status as the host reads it (pinned host memory that the GPU writes).
+struct HostStatus {
+    int flags[kNumFlags];
+    double time;
+};
+
+// Report the flags and the time and clear the flags (all but that of the mesh).
+__device__ inline void report_status(HostStatus *host, int *flags, const double *time)
+{
+    for (int f = 0; f < kNumFlags; ++f) {
+        host->flags[f] = __hip_atomic_load(&flags[f], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (f != kFlagBadJ) flags[f] = 0;
+    }
+    host->time = *time;
+}
+
 // A step exceeds the bounds of the state it produced when it is above this
 // many times the smaller of the CFL and viscous ones (the factors cfl and
 // cfl_visc are inside the bounds).
@@ -1865,6 +1885,7 @@ struct DtArgs {
     double *dt;                // per instance k: dt[8k..8k+3] step and its bounds, dt[8k+4] time
     int mode;                  // DtMode
     int *flags, *iflags;
+    HostStatus *host;          // check: the flags go here (nullptr: they stay)
 };
 
 __device__ __forceinline__ void slot_min(unsigned long long *slot, double v)
@@ -2134,6 +2155,7 @@ __device__ __forceinline__ void dt_finish(const DtArgs<R> &a, int k, unsigned id
                     atomicOr(&a.flags[kFlagStepBound], 1);
                     if (a.iflags) atomicOr(&a.iflags[k], 2);
                 }
+                if (a.host) report_status(a.host, a.flags, dt + 4);
             } else {
                 double step = fmin(cfl, visc);
                 if (a.P.limiter_on) step = fmin(step, pos);

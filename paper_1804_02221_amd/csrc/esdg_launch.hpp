@@ -8,6 +8,7 @@ namespace esdg {
 
 template <typename R> struct Tab;
 template <typename R> struct Phys;
+struct HostStatus;
 
 // Device buffers of one context (typed views are cast per precision).
 struct Bufs {
@@ -88,8 +89,8 @@ struct Launch {
     static hipError_t stage(const Bufs &B, const StageCall &c, const Phys<R> &P, const Tab<R> &t,
                             hipStream_t s, Ev ev);
     static hipError_t limit(const Bufs &B, int buf, const Phys<R> &P, const Tab<R> &t, hipStream_t s);
-    static hipError_t dt(const Bufs &B, int in, bool av, bool fused, int mode, const Phys<R> &P, hipStream_t s,
-                         Ev ev);
+    static hipError_t dt(const Bufs &B, int in, bool av, bool fused, int mode, HostStatus *host, const Phys<R> &P,
+                         hipStream_t s, Ev ev);
     static hipError_t adjoint_stage(const Bufs &B, const AdjCall &c, const Phys<R> &P, const Tab<R> &t,
                                     hipStream_t s, Ev ev);
     static hipError_t bathymetry_adjoint(const Bufs &B, const Tab<double> &td, const double *gbx,

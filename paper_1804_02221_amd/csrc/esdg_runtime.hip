@@ -89,6 +89,13 @@ __global__ void scale_step_kernel(double *dt, double f, double *tacc)
     }
 }
 
+// Flags and time to the host's status block, in one launch: two copies with a
+// wait each took longer than a step of a small mesh.
+__global__ void report_status_kernel(HostStatus *host, int *flags, const double *time)
+{
+    if (threadIdx.x == 0) report_status(host, flags, time);
+}
+
 // p[8k] = v for the n instances k (times live at dscal[8k + 4]).
 __global__ void set_scalar_kernel(double *p, double v, int n)
 {
@@ -240,6 +247,7 @@ struct esdg_ctx {
     bool use_graphs = true;
     hipStream_t cap_stream = nullptr;   // private stream the graphs are captured on
     hipEvent_t tune_ev[2] = {nullptr, nullptr};   // the autotuner's own timing events
+    HostStatus *host = nullptr;   // pinned; written by the GPU (report_status)
     int64_t last_limited = 0;   // limited element-stages of the last esdg_step call
     // instances (ensembles): element ranges [inst_off[k], inst_off[k+1]) in
     // the caller's order and, since the locality order permutes inside each
@@ -484,7 +492,7 @@ int launch_dt(esdg_ctx *ctx, int buf, int mode)
     return timed(ctx, kProfDt, [&](Ev ev) {
         return dispatch(ctx, [&](auto L, auto r) {
             using R = decltype(r);
-            return decltype(L)::dt(ctx->B, buf, av, fused, mode, phys<R>(ctx), ctx->stream, ev);
+            return decltype(L)::dt(ctx->B, buf, av, fused, mode, nullptr, phys<R>(ctx), ctx->stream, ev);
         });
     });
 }
@@ -500,13 +508,14 @@ int launch_fixed_step(esdg_ctx *ctx, double dt)
 }
 
 // Check of the step just taken against the bounds of its result: the last
-// stage left them, and they stay current for the next step's pass.
-int launch_step_check(esdg_ctx *ctx)
+// stage left them, and they stay current for the next step's pass.  host: where
+// the flags are reported (and cleared), or nullptr.
+int launch_step_check(esdg_ctx *ctx, HostStatus *host)
 {
     return dispatch(ctx, [&](auto L, auto r) {
                using R = decltype(r);
-               return decltype(L)::dt(ctx->B, ctx->cur, ctx->P.av_on != 0, true, kDtCheck, phys<R>(ctx), ctx->stream,
-                                      Ev{});
+               return decltype(L)::dt(ctx->B, ctx->cur, ctx->P.av_on != 0, true, kDtCheck, host, phys<R>(ctx),
+                                      ctx->stream, Ev{});
            }) == hipSuccess
                ? ESDG_OK
                : fail(ctx, ESDG_EHIP, "launch of the step check failed");
@@ -519,10 +528,16 @@ int reset_flags(esdg_ctx *ctx)
     return ESDG_OK;
 }
 
-int read_flags(esdg_ctx *ctx, int flags[kNumFlags])
+// Flags (cleared on the device) and, t not null, the time, behind everything on
+// the stream.
+int read_flags(esdg_ctx *ctx, int flags[kNumFlags], double *t = nullptr)
 {
-    CK(hipMemcpyAsync(flags, ctx->B.flags, kNumFlags * sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+    hipLaunchKernelGGL(report_status_kernel, dim3(1), dim3(64), 0, ctx->stream, ctx->host, ctx->B.flags,
+                       (const double *)ctx->B.dscal + 4);
+    CK(hipGetLastError());
     CK(hipStreamSynchronize(ctx->stream));
+    std::copy(ctx->host->flags, ctx->host->flags + kNumFlags, flags);
+    if (t) *t = ctx->host->time;
     return ESDG_OK;
 }
 
@@ -851,6 +866,10 @@ int esdg_create(esdg_ctx **out, int device, int precision)
     if (!c) return ESDG_ENOMEM;
     c->device = device;
     c->prec = precision;
+    if (hipHostMalloc((void **)&c->host, sizeof(HostStatus), hipHostMallocDefault) != hipSuccess) {
+        delete c;
+        return ESDG_ENOMEM;
+    }
     esdg_default_params(&c->P, 3);
     *out = c;
     return ESDG_OK;
@@ -863,6 +882,7 @@ int esdg_destroy(esdg_ctx *ctx)
     if (ctx->stream) (void)hipStreamSynchronize(ctx->stream);
     free_bufs(ctx);
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
+    if (ctx->host) (void)hipHostFree(ctx->host);
     for (hipEvent_t e : ctx->ev_pool) (void)hipEventDestroy(e);
     for (hipEvent_t e : ctx->tune_ev)
         if (e) (void)hipEventDestroy(e);
@@ -1229,6 +1249,8 @@ int esdg_step(esdg_ctx *ctx, int nsteps, double dt, double *t_out)
     if (retries > 0 && n_inst(ctx) > 1) return fail(ctx, ESDG_EINVAL, "dt retries need a single instance");
     TRY(reset_flags(ctx));
     int status = ESDG_OK;
+    int flags[kNumFlags];
+    double t = 0.0;
     for (int it = 0; it < nsteps; ++it) {
         if (retries <= 0) {
             if (graph_ready(ctx, dt)) TRY(graph_step(ctx, dt));
@@ -1236,7 +1258,6 @@ int esdg_step(esdg_ctx *ctx, int nsteps, double dt, double *t_out)
             continue;
         }
         const int base = ctx->cur;
-        TRY(reset_flags(ctx));
         for (int attempt = 0;; ++attempt) {
             if (attempt == 0) {
                 TRY(launch_one_step(ctx, dt));
@@ -1245,9 +1266,11 @@ int esdg_step(esdg_ctx *ctx, int nsteps, double dt, double *t_out)
                 ctx->cur = base;
                 TRY(launch_one_step(ctx, dt, false));
             }
-            TRY(launch_step_check(ctx));
-            int flags[kNumFlags];
-            TRY(read_flags(ctx, flags));
+            // the check's last workgroup reports the flags and the time
+            TRY(launch_step_check(ctx, ctx->host));
+            CK(hipStreamSynchronize(ctx->stream));
+            std::copy(ctx->host->flags, ctx->host->flags + kNumFlags, flags);
+            t = ctx->host->time;
             if (flags[kFlagNonFinite]) break;   // reported below; halving the step cannot help
             if (!(flags[kFlagNegMean] || flags[kFlagStepBound]) || attempt >= retries) {
                 // out of retries a step above the bounds of its result is kept
@@ -1260,15 +1283,11 @@ int esdg_step(esdg_ctx *ctx, int nsteps, double dt, double *t_out)
             hipLaunchKernelGGL(scale_step_kernel, dim3(1), dim3(1), 0, ctx->stream, ctx->B.dscal, 0.5,
                                ctx->B.dscal + 4);
             CK(hipGetLastError());
-            TRY(reset_flags(ctx));
         }
     }
-    int flags[kNumFlags];
-    TRY(read_flags(ctx, flags));
-    if (t_out) {
-        CK(hipMemcpyAsync(t_out, ctx->B.dscal + 4, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-        CK(hipStreamSynchronize(ctx->stream));
-    }
+    // (with the check the flags are those of the last attempt)
+    if (retries <= 0 || nsteps == 0) TRY(read_flags(ctx, flags, &t));
+    if (t_out) *t_out = t;
     ctx->last_limited = flags[kFlagLimited];
     if (flags[kFlagNonFinite]) return fail(ctx, ESDG_ENONFINITE, "non-finite value in a stage output");
     if (flags[kFlagDtPos]) return fail(ctx, ESDG_EDTPOS, "no admissible time step");
@@ -1801,7 +1820,7 @@ int group_attempt(esdg_ctx *ctx, int base, bool first, int *hflags)
         ctx->masked_attempt = false;
         TRY(st);
     }
-    TRY(launch_step_check(ctx));
+    TRY(launch_step_check(ctx, nullptr));
     CK(hipMemcpyAsync(hflags, ctx->B.flags, kNumFlags * sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
     CK(hipMemcpyAsync(hflags + kNumFlags, ctx->B.iflags, ni * sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
     return ESDG_OK;
