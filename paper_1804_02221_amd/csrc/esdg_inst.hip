@@ -2,6 +2,7 @@
 // build, one object file per degree so the degrees compile in parallel).
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "esdg_adjoint.hpp"
@@ -224,8 +225,12 @@ hipError_t Launch<N, R>::dt(const Bufs &B, int in, bool av, bool fused, int mode
     // (one per thread, the rest of the unroll clamped away, took 15 us at
     // 524288 face nodes and 4.7 more to reduce the minima; now 11.6 in all)
     constexpr int64_t np = (N + 1) * (N + 1), per = (int64_t)kDtThreads * kXcds;
-    const int64_t items = fused ? (B.K * 4 * (N + 1) + kDtUnroll - 1) / kDtUnroll : B.K * np;
-    const int64_t want = ((items + per - 1) / per) * kXcds;
+    const bool faces = P.limiter_on && mode != kDtCheck;
+    const int64_t nfn = faces ? (B.K * 4 * (N + 1) + kDtUnroll - 1) / kDtUnroll : 0;
+    const int64_t items = std::max(fused ? B.K : B.K * np, nfn);
+    // up to kDtOne items a thread one workgroup is enough and needs no atomics
+    // (16^2 elements at N = 3 without limiter: 4.7 -> 3.3 us)
+    const int64_t want = items <= kDtOne * kDtThreads ? 1 : ((items + per - 1) / per) * kXcds;
     const unsigned grid = (unsigned)(want < (int64_t)kDtMaxBlocks ? want : (int64_t)kDtMaxBlocks);
     launch_ev(dt_kernel<N, R>, dim3(grid), dim3(kDtThreads), s, ev, a);
     return hipGetLastError();

@@ -1828,6 +1828,7 @@ __global__ __launch_bounds__(Shape<N>::T) void limit_kernel(Mesh<R> m, Phys<R> P
 constexpr int kDtThreads = 256;
 constexpr unsigned kDtMaxBlocks = 2048;
 constexpr int kDtUnroll = 4;        // face nodes a thread evaluates at once
+constexpr int64_t kDtOne = 4;       // rounds that one workgroup takes alone before more share them
 // Ticket counters of an instance: each workgroup counts in one of the first
 // kDtTickets, the last of each in the one behind them (a single counter would
 // serialise up to 2048 atomics on one address).
@@ -1964,6 +1965,12 @@ struct XcdRange {
     int64_t b, e, stride;
     __device__ XcdRange(int64_t n, int T)
     {
+        if (gridDim.x == 1) {   // (dt_kernel on a small mesh)
+            b = threadIdx.x;
+            e = n;
+            stride = T;
+            return;
+        }
         const int64_t per = (n + kXcds - 1) / kXcds;
         const int64_t lo = (int64_t)(blockIdx.x % kXcds) * per;
         const int64_t hi = lo + per < n ? lo + per : n;
@@ -2072,9 +2079,11 @@ __device__ __forceinline__ R cfl_node(const DtArgs<R> &a, int64_t q)
     return cfl_bound<N, R>(a.h[q], a.hu[q], a.hv[q], Ax, Cx, Ae, Ce, Ce * Ax - Cx * Ae, a.P);
 }
 
-// Workgroup minima of the three bounds into slots[3][kDtSlots] (slot sl).
+// Workgroup minima of the three bounds into slots[3][kDtSlots] (slot sl), or,
+// with own, to own[3] in LDS (+inf where there is none).
 template <typename R>
-__device__ __forceinline__ void dt_block_min(R cflb, R viscb, R posb, unsigned long long *slots, int sl)
+__device__ __forceinline__ void dt_block_min(R cflb, R viscb, R posb, unsigned long long *slots, int sl,
+                                             double *own = nullptr)
 {
     constexpr int T = kDtThreads;
     __shared__ R s_w[3][T / 64];
@@ -2092,7 +2101,8 @@ __device__ __forceinline__ void dt_block_min(R cflb, R viscb, R posb, unsigned l
         R v = s_w[t][0];
 #pragma unroll
         for (int w = 1; w < T / 64; ++w) v = s_w[t][w] < v ? s_w[t][w] : v;
-        if (v < R(1.0e38)) slot_min(&slots[t * kDtSlots + sl], (double)v);
+        if (own) own[t] = v >= R(0) && v < R(1.0e38) ? (double)v : __builtin_huge_val();
+        else if (v < R(1.0e38)) slot_min(&slots[t * kDtSlots + sl], (double)v);
     }
     lds_sync<T>();
 }
@@ -2105,6 +2115,32 @@ __device__ __forceinline__ double take_slots(unsigned long long *slots, int lane
     const unsigned long long v = __hip_atomic_load(&slots[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     slots[lane] = 0x7FF0000000000000ull;
     return wave_min(__longlong_as_double((long long)v));
+}
+
+// What a.mode asks with instance k's minima (one thread).
+template <typename R>
+__device__ __forceinline__ void dt_conclude(const DtArgs<R> &a, int k, double cfl, double visc, double pos)
+{
+    double *const dt = a.dt + 8 * (int64_t)k;
+    if (a.mode == kDtCheck) {
+        if (dt[0] > kStepBoundFactor * fmin(cfl, visc)) {
+            atomicOr(&a.flags[kFlagStepBound], 1);
+            if (a.iflags) atomicOr(&a.iflags[k], 2);
+        }
+        if (a.host) report_status(a.host, a.flags, dt + 4);
+        return;
+    }
+    double step = fmin(cfl, visc);
+    if (a.P.limiter_on) step = fmin(step, pos);
+    if (!(step > 0.0) || !(step < __builtin_huge_val())) {
+        atomicOr(&a.flags[kFlagDtPos], 1);
+        step = 0.0;
+    }
+    dt[0] = step;
+    dt[1] = cfl;
+    dt[2] = visc;
+    dt[3] = pos;
+    if (a.mode == kDtAdvance) dt[4] += step;
 }
 
 // Called by every workgroup when its minima of instance k are in the slots:
@@ -2150,27 +2186,7 @@ __device__ __forceinline__ void dt_finish(const DtArgs<R> &a, int k, unsigned id
         }
         __syncthreads();
         if (t == 0) {
-            double *const dt = a.dt + 8 * (int64_t)k;
-            const double cfl = s_min[0], visc = s_min[1], pos = s_min[2];
-            if (a.mode == kDtCheck) {
-                if (dt[0] > kStepBoundFactor * fmin(cfl, visc)) {
-                    atomicOr(&a.flags[kFlagStepBound], 1);
-                    if (a.iflags) atomicOr(&a.iflags[k], 2);
-                }
-                if (a.host) report_status(a.host, a.flags, dt + 4);
-            } else {
-                double step = fmin(cfl, visc);
-                if (a.P.limiter_on) step = fmin(step, pos);
-                if (!(step > 0.0) || !(step < __builtin_huge_val())) {
-                    atomicOr(&a.flags[kFlagDtPos], 1);
-                    step = 0.0;
-                }
-                dt[0] = step;
-                dt[1] = cfl;
-                dt[2] = visc;
-                dt[3] = pos;
-                if (a.mode == kDtAdvance) dt[4] += step;
-            }
+            dt_conclude<R>(a, k, s_min[0], s_min[1], s_min[2]);
         }
     }
     __syncthreads();   // the next chunk's minima and tickets
@@ -2210,6 +2226,12 @@ __global__ __launch_bounds__(kDtThreads) void dt_kernel(DtArgs<R> a)
     if (a.P.limiter_on && a.mode != kDtCheck) {
         const XcdRange r(K * 4 * nf, T);
         posb = lemma2_min<N, R, kDtUnroll>(a, r.b, r.e, r.stride);
+    }
+    if (gridDim.x == 1) {
+        __shared__ double s_own[3];
+        dt_block_min<R>(cflb, viscb, posb, nullptr, 0, s_own);
+        if (threadIdx.x == 0) dt_conclude<R>(a, 0, s_own[0], s_own[1], s_own[2]);
+        return;
     }
     dt_block_min<R>(cflb, viscb, posb, a.slots, blockIdx.x % kDtSlots);
     dt_finish<R>(a, 0, blockIdx.x, gridDim.x);

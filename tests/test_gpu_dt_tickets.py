@@ -1,7 +1,7 @@
 """GPU: the time-step pass that reduces its own minima.  Meshes whose pass
-takes 8, 32, 40 and 144 workgroups: one ticket counter, exactly full, just two
-levels, two levels with unequal shares; each pass must leave slots and
-counters as the next one needs them."""
+takes 1, 8, 32, 40 and 144 workgroups: no atomics, one ticket counter, exactly
+full, just two levels, two levels with unequal shares; each pass must leave
+slots and counters as the next one needs them."""
 import numpy as np
 import pytest
 
@@ -11,7 +11,7 @@ import oracle
 from paper_1804_02221_amd.inputs import smooth_sweep
 
 
-@pytest.mark.parametrize("n", [5, 40, 48, 96])
+@pytest.mark.parametrize("n", [5, 20, 40, 48, 96])
 def test_step_from_one_launch(n):
     """Step, CFL and mean-positivity bound against the oracle on the state that
     one step left.  Each is a handful of operations without cancellation on
