@@ -379,8 +379,8 @@ constexpr bool kFreshLanes = sizeof(R) == 8 || N == 5;
 // geometry_kernel in the same order (so bit for bit the stored values): 16
 // fewer bytes per node and stage for 4(N+1) multiply-adds and two more
 // workgroup barriers.  Measured on the stage kernel: 3-7% faster at N = 2..4,
-// 5-7% slower at N = 5..8, where the registers it holds across the face
-// prefetch cost occupancy or spills.  In single precision the four metric
+// 2% slower at N = 5 and 6% at N = 7, where the longer sums and the registers
+// it holds across the face prefetch cost more than the bytes.  In single precision the four metric
 // terms take as many bytes as the two float64 coordinates.
 template <int N, typename R>
 constexpr bool kMetricInKernel = sizeof(R) == 8 && N <= 4;
@@ -1314,7 +1314,6 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
     // when they evaluate it.
     constexpr int NS = (NF + T - 1) / T;
     FacePrefetch<R> pf0;
-    // (a one-trip loop here costs a VGPR and a dozen spilled SGPRs at N = 7)
     prefetch_face<N, R, E, NF>(a, t, e0, pf0);
     // has this lane's element viscosity (a lane mask; the value itself is
     // read again where it is used)
