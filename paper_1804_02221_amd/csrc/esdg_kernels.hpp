@@ -91,8 +91,11 @@ struct StageCfg {
     static constexpr int waves = V == 2 ? base_waves - 1 : base_waves;
     // partner-loop unroll, double and single precision: at N = 7 the doubles'
     // by two (a smooth flow even; with wet/dry tiles at 128^2 40.4 -> 39.6 us,
-    // fewer registers being spilled on them)
-    static constexpr int VU = (V >= 3 || N == 7) ? 2 : N + 1, VU32 = V >= 3 ? 2 : N + 1;
+    // fewer registers being spilled on them), the floats' at N = 6 and 8, where
+    // eight waves per SIMD spill 13 and 10 registers of the full unroll (512^2:
+    // 294 -> 272 and 489 -> 454 us; with seven waves the full one is as good)
+    static constexpr int VU = (V >= 3 || N == 7) ? 2 : N + 1;
+    static constexpr int VU32 = (V >= 3 || (V == 0 && (N == 6 || N == 8))) ? 2 : N + 1;
     // Variant 4 avoids the LDS bank conflicts of the eta-direction partner
     // reads (a wave reads column mm of every row, rows 16(N+1) bytes apart in
     // FP64: at N = 7 eight rows on two bank groups).  At N = 7 the columns of
@@ -1450,11 +1453,15 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
         // sums of D dA and D dC over both directions are the discrete metric
         // identities (D_xi y_eta = D_eta y_xi, the terms being D's own
         // derivatives of the coordinates): zero, left out, and with them the
-        // rounding of the stored terms that they would add.  18 operations a
-        // partner; with the jumps of A and C and those sums kept it was 27,
-        // and this kernel is
-        // bound by vector instructions: N = 7, 384^2 185 -> 174 us, N = 8,
-        // 150^2 42.5 -> 38.5.
+        // rounding of the stored terms that they would add.  sA is pA, the same
+        // for the whole line, plus the partner's small am.x: the sums of d dhu,
+        // d dhv and d dh meet pA and pC after the loop (Hu, Hv, H), so that A1,
+        // C2 and C3 are not rounded at full size per partner.  22 operations a
+        // partner, against 27 with the jumps of A and C and their sums; this
+        // kernel is bound by vector instructions.  N = 7, 512^2: a stage
+        // 303 us; the right-hand side's mass error 7.4e-7 -> 6.3e-7 of its
+        // maximum (N = 8: 8.2e-7 -> 5.1e-7).  With e and dh sA summed as they
+        // are it is 18 operations and 296 us, but errors of 1.1e-6 for both.
         const int base = el * PS;
         constexpr int VU = StageCfg<N, V>::VU32;
         // (the staged and own terms are relative to the element's middle
@@ -1462,32 +1469,45 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
         // reference)
         const R *const mr = s_mref + 4 * el;
         const R hu2 = R(2) * hu, hv2 = R(2) * hv;
-        auto pair = [&](R d, V2 am, V2 qm, V2 wm, R hm, R pA, R pC) {
-            const R sA = pA + am.x, sC = pC + am.y;
-            const R e = (qm.x - hu) * sA + (qm.y - hv) * sC;
-            const R dF = d * (hu2 * sA + hv2 * sC + e);
+        auto pair = [&](R d, V2 am, V2 qm, V2 wm, R hm, R pA, R pC, R F0, R &H, R &Hu, R &Hv) {
+            const R dhu = qm.x - hu, dhv = qm.y - hv;
+            const R q = dhu * am.x + dhv * am.y;
+            const R dF = d * (q + (dhu * pA + (dhv * pC + (hu2 * am.x + (hv2 * am.y + F0)))));
             const R dh = d * (hm - h);
-            A1 += d * e;
+            Hu += d * dhu;
+            Hv += d * dhv;
+            A1 += d * q;
             A2 += dF * (wm.x - u);
             A3 += dF * (wm.y - v);
-            C2 += dh * sA;
-            C3 += dh * sC;
+            H += dh;
+            C2 += dh * am.x;
+            C3 += dh * am.y;
         };
         {
             const R pA = Ax + R(2) * mr[0], pC = Cx + R(2) * mr[1];
+            const R F0 = hu2 * pA + hv2 * pC;
+            R H = 0, Hu = 0, Hv = 0;
 #pragma unroll VU
             for (int mm = 0; mm < nf; ++mm) {
                 const int qq = base + mm * RS + stage_col<N, V>(mm, j);
-                pair(s_dz[i * nf + mm], s_a[qq], s_q[qq], s_w[qq], s_h[qq], pA, pC);
+                pair(s_dz[i * nf + mm], s_a[qq], s_q[qq], s_w[qq], s_h[qq], pA, pC, F0, H, Hu, Hv);
             }
+            C2 += H * pA;
+            A1 += Hu * pA + Hv * pC;
+            C3 += H * pC;
         }
         {
             const R pA = Ae + R(2) * mr[2], pC = Ce + R(2) * mr[3];
+            const R F0 = hu2 * pA + hv2 * pC;
+            R H = 0, Hu = 0, Hv = 0;
 #pragma unroll VU
             for (int mm = 0; mm < nf; ++mm) {
                 const int qq = base + i * RS + stage_col<N, V>(i, mm);
-                pair(s_dz[j * nf + mm], s_b[qq], s_q[qq], s_w[qq], s_h[qq], pA, pC);
+                pair(s_dz[j * nf + mm], s_b[qq], s_q[qq], s_w[qq], s_h[qq], pA, pC, F0, H, Hu, Hv);
             }
+            C2 += H * pA;
+            A1 += Hu * pA + Hv * pC;
+            C3 += H * pC;
         }
     } else {
         const int base = el * PS;
