@@ -1010,7 +1010,7 @@ struct StageArgs {
     const double *dt;            // per instance k: the current step at dt[8k]
     R ca, cb;                    // LSRK a_k, b_k; SSP alpha_k, beta_k
     int *flags;                  // status flags (kFlag*)
-    int *iflags;                 // ensembles with step retries: per-instance flags (1: negative mean), else nullptr
+    int *iflags;                 // [instance] step flags that ensembles with step retries read (1: negative mean)
     const int *imask;            // with inst: only elements of instances k with imask[k] != 0 (a retry of
                                  // some instances), else nullptr
     int64_t ntiles;
@@ -1688,7 +1688,7 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
                     if (mh < R(0)) {
                         th = R(0);
                         atomicOr(&late.flags[kFlagNegMean], 1);
-                        if (late.iflags) atomicOr(&late.iflags[late.inst ? late.inst[e] : 0], 1);
+                        atomicOr(&late.iflags[late.inst ? late.inst[e] : 0], 1);
                     } else {
                         th = mh / (mh - mn);
                         th = th < R(1) ? th : R(1);
@@ -1886,8 +1886,8 @@ constexpr double kStepBoundFactor = 2.0;
 // What the pass does with the minima: set each instance's step (and add it to
 // its time when advance), or check the step that produced the state against
 // them (a-posteriori check, reading of the remark that the step is adjusted
-// when a smaller one is found to be needed, section 6): raise kFlagStepBound,
-// and with iflags bit 2 of the instance's flag, and leave the step as it is.
+// when a smaller one is found to be needed, section 6): raise kFlagStepBound
+// and bit 2 of the instance's flag, and leave the step as it is.
 enum DtMode { kDtSet = 0, kDtAdvance = 1, kDtCheck = 2 };
 
 template <typename R>
@@ -2144,7 +2144,7 @@ __device__ __forceinline__ void dt_conclude(const DtArgs<R> &a, int k, double cf
     if (a.mode == kDtCheck) {
         if (dt[0] > kStepBoundFactor * fmin(cfl, visc)) {
             atomicOr(&a.flags[kFlagStepBound], 1);
-            if (a.iflags) atomicOr(&a.iflags[k], 2);
+            atomicOr(&a.iflags[k], 2);
         }
         if (a.host) report_status(a.host, a.flags, dt + 4);
         return;

@@ -36,12 +36,12 @@ struct Bufs {
     double *dscal = nullptr; // per instance k: [8k..8k+3] dt and its bounds, [8k+4] time, [8k+5..7] spare
     unsigned long long *slots = nullptr;  // [instance][3][kDtSlots]
     unsigned *tickets = nullptr;          // [instance][kDtTickets + 1]
-    int n_inst = 1;          // instances (ensembles); > 1: the arrays below are set
+    int n_inst = 1;          // instances (ensembles); > 1: inst and chunk are set
     int32_t *inst = nullptr;    // [K] instance of each internal element
     void *chunk = nullptr;      // [nchunks] DtChunk: element chunks of the time-step pass (never across instances)
     int64_t nchunks = 0;
     int *flags = nullptr;    // status flags (kFlag* in esdg_kernels.hpp)
-    int *iflags = nullptr;   // [n_inst] per-instance step flags (ensembles): 1 negative mean, 2 step above its result's bounds
+    int *iflags = nullptr;   // [n_inst] per-instance step flags (read by ensembles): 1 negative mean, 2 step above its result's bounds
     int *imask = nullptr;    // [n_inst] instances whose step is redone at half the size (ensembles)
     double *part = nullptr;  // diagnostics partial sums
     int64_t part_cap = 0;

@@ -1100,6 +1100,10 @@ int upload_mesh_impl(esdg_ctx *ctx, int N, int64_t K, const double *x, const dou
     TRY(alloc(ctx, &B.slots, (size_t)3 * kDtSlots * ni * sizeof(unsigned long long)));
     TRY(alloc(ctx, &B.tickets, (size_t)(kDtTickets + 1) * ni * sizeof(unsigned)));
     CK(hipMemsetAsync(B.tickets, 0, (size_t)(kDtTickets + 1) * ni * sizeof(unsigned), ctx->stream));
+    // (a degree's only instance of an ensemble with the step check has them too)
+    TRY(alloc(ctx, &B.iflags, ni * sizeof(int)));
+    TRY(alloc(ctx, &B.imask, ni * sizeof(int)));
+    CK(hipMemsetAsync(B.iflags, 0, ni * sizeof(int), ctx->stream));
     B.n_inst = ni;
     if (ni > 1) {
         // instance of every (internal) element and chunks of the time-step pass
@@ -1116,9 +1120,6 @@ int upload_mesh_impl(esdg_ctx *ctx, int N, int64_t K, const double *x, const dou
         }
         B.nchunks = (int64_t)chunks.size();
         TRY(alloc(ctx, &B.inst, K * sizeof(int32_t)));
-        TRY(alloc(ctx, &B.iflags, ni * sizeof(int)));
-        TRY(alloc(ctx, &B.imask, ni * sizeof(int)));
-        CK(hipMemsetAsync(B.iflags, 0, ni * sizeof(int), ctx->stream));
         TRY(alloc(ctx, &B.chunk, chunks.size() * sizeof(DtChunk)));
         CK(hipMemcpyAsync(B.inst, inst_of.data(), K * sizeof(int32_t), hipMemcpyHostToDevice, ctx->stream));
         CK(hipMemcpyAsync(B.chunk, chunks.data(), chunks.size() * sizeof(DtChunk), hipMemcpyHostToDevice, ctx->stream));
