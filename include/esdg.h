@@ -402,8 +402,8 @@ int esdg_gauge_values(esdg_ctx *ctx, double *H, int mem);
  * *loss (may be NULL) receives L and H (may be NULL) the gauge values
  * [nsteps][ng].  The state is advanced as by esdg_step; the states at steps
  * 0, every, 2 every, ... are kept on the device for esdg_adjoint_backward
- * (ceil(nsteps/every) states, plus S every + 1 stage states during the
- * backward sweep, S = 5 stages per LSRK step, 3 per SSPRK step).
+ * (ceil(nsteps/every) states, plus S every + 1 stage states taken by the
+ * first backward sweep, S = 5 stages per LSRK step, 3 per SSPRK step).
  * ESDG_EINVAL if the limiter acted in any stage.
  */
 int esdg_adjoint_forward(esdg_ctx *ctx, int nsteps, double dt, int every, const double *target, int mem,
@@ -412,8 +412,9 @@ int esdg_adjoint_forward(esdg_ctx *ctx, int nsteps, double dt, int every, const 
 /*
  * Reverse sweep of the last esdg_adjoint_forward: gb = seed * dL/db (the
  * initial state held fixed) and, when not NULL, g{h,hu,hv}0 = seed * dL/dW(0).
- * Each segment between checkpoints is recomputed from its checkpoint, then
- * its stages are reversed.  Leaves the current state alone.  ESDG_EINVAL if
+ * Each segment between checkpoints is recomputed from its checkpoint (but the
+ * last where the forward sweep found an earlier reverse sweep's memory to keep
+ * its stages in), then its stages are reversed.  Leaves the current state alone.  ESDG_EINVAL if
  * no forward sweep is recorded or the bathymetry or the parameters changed
  * since.  (For an
  * initial state set through the surface, h(0) = H0 - b, the total gradient
