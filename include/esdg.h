@@ -278,7 +278,7 @@ int esdg_profile_read_kernels(esdg_ctx *ctx, double ms[6], int64_t launches[6]);
  * else 256 threads) with its register budget and partner-loop unroll; 1 the
  * alternative workgroup size (256 threads at N = 3 and 7, 64 at N = 2, else
  * 128); 2 the default tile with one wave per SIMD less in its
- * register budget; 3 the default tile with a smaller partner-loop unroll;
+ * register budget; 3 the default tile with the other partner-loop unroll;
  * 4 the default tile with bank-conflict-free staging rows: padded by one
  * node (the paper's LDS padding, more LDS per tile), at N = 7 XOR-swizzled
  * columns instead (no more LDS).

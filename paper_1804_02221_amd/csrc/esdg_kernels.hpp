@@ -67,8 +67,10 @@ struct TileShape {
 //   0  the default tile, its register budget and partner unroll;
 //   1  the alternative workgroup size (StageThreads), no register budget;
 //   2  the default tile with one wave per SIMD less in its register budget
-//      (more registers);
-//   3  the default tile with the partner loops unrolled by two;
+//      (more registers where the budget binds: FP64 at N = 2, 3 and 8 takes
+//      88-94 with either);
+//   3  the default tile with the other partner unroll (by two, or fully where
+//      the default is by two: N = 7 in FP64, N = 6 and 8 in FP32);
 //   4  the default tile with bank-conflict-free staging rows: padded by one
 //      node (the paper's LDS padding, appendix C), or at N = 7 XOR-swizzled
 //      columns (no more LDS; StageCfg::SWZ); unrolled by two (a full unroll
@@ -93,9 +95,11 @@ struct StageCfg {
     // by two (a smooth flow even; with wet/dry tiles at 128^2 40.4 -> 39.6 us,
     // fewer registers being spilled on them), the floats' at N = 6 and 8, where
     // eight waves per SIMD spill 13 and 10 registers of the full unroll (512^2:
-    // 294 -> 272 and 489 -> 454 us; with seven waves the full one is as good)
-    static constexpr int VU = (V >= 3 || N == 7) ? 2 : N + 1;
-    static constexpr int VU32 = (V >= 3 || (V == 0 && (N == 6 || N == 8))) ? 2 : N + 1;
+    // 294 -> 272 and 489 -> 454 us; with seven waves the full one is as good);
+    // variant 3 takes the other one of two and full
+    static constexpr bool by_two = N == 7, by_two32 = N == 6 || N == 8;
+    static constexpr int VU = (V == 4 || by_two != (V == 3)) ? 2 : N + 1;
+    static constexpr int VU32 = (V == 4 || (V == 3 ? !by_two32 : V == 0 && by_two32)) ? 2 : N + 1;
     // Variant 4 avoids the LDS bank conflicts of the eta-direction partner
     // reads (a wave reads column mm of every row, rows 16(N+1) bytes apart in
     // FP64: at N = 7 eight rows on two bank groups).  At N = 7 the columns of
