@@ -1854,8 +1854,12 @@ constexpr int kDtUnroll = 4;        // face nodes a thread evaluates at once
 constexpr int64_t kDtOne = 4;       // rounds that one workgroup takes alone before more share them
 // Ticket counters of an instance: each workgroup counts in one of the first
 // kDtTickets, the last of each in the one behind them (a single counter would
-// serialise up to 2048 atomics on one address).
+// serialise up to 2048 atomics on one address), every counter in a cache line
+// of its own: atomics on one line are taken one after the other wherever they
+// point, and with all counters in two lines the bounds of a new state at 128^2,
+// N = 5 without viscosity and limiter took 42.4 us a call (now 35.7).
 constexpr int kDtTickets = 32;
+constexpr int kDtTicketStride = 128 / sizeof(unsigned);
 
 // One chunk of the ensemble time-step pass: elements [lo, hi) of instance
 // inst, its index among that instance's n chunks.
@@ -1907,7 +1911,7 @@ struct DtArgs {
     unsigned long long *slots; // [instance][3][kDtSlots]
     const DtChunk *chunk;      // ensembles: [nchunks] element chunks, none across instances
     int64_t nchunks;
-    unsigned *tickets;         // [instance][kDtTickets + 1], zero between launches
+    unsigned *tickets;         // [instance][kDtTickets + 1][kDtTicketStride], zero between launches
     double *dt;                // per instance k: dt[8k..8k+3] step and its bounds, dt[8k+4] time
     int mode;                  // DtMode
     int *flags, *iflags;
@@ -2183,18 +2187,19 @@ __device__ __forceinline__ void dt_finish(const DtArgs<R> &a, int k, unsigned id
     const int t = threadIdx.x;
     // (behind dt_block_min's last barrier its three lanes' atomics have returned)
     if (t == 0) {
-        unsigned *const tk = a.tickets + (int64_t)k * (kDtTickets + 1);
+        unsigned *const tk = a.tickets + (int64_t)k * (kDtTickets + 1) * kDtTicketStride;
         // (few workgroups: one counter)
         const unsigned sub = idx % kDtTickets, in_sub = (n - sub + kDtTickets - 1) / kDtTickets;
         const bool two = n > (unsigned)kDtTickets;
         bool up = !two;
-        if (two && atomicAdd(&tk[sub], 1u) == in_sub - 1) {
-            atomicExch(&tk[sub], 0u);
+        unsigned *const mine = tk + sub * kDtTicketStride, *const all = tk + kDtTickets * kDtTicketStride;
+        if (two && atomicAdd(mine, 1u) == in_sub - 1) {
+            atomicExch(mine, 0u);
             up = true;
         }
         int last = 0;
-        if (up && atomicAdd(&tk[kDtTickets], 1u) == (two ? (unsigned)kDtTickets : n) - 1) {
-            atomicExch(&tk[kDtTickets], 0u);
+        if (up && atomicAdd(all, 1u) == (two ? (unsigned)kDtTickets : n) - 1) {
+            atomicExch(all, 0u);
             last = 1;
         }
         s_last = last;

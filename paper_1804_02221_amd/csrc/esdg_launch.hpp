@@ -35,7 +35,7 @@ struct Bufs {
     int *count = nullptr;    // number of elements with eps > 0 (esdg_step_stats)
     double *dscal = nullptr; // per instance k: [8k..8k+3] dt and its bounds, [8k+4] time, [8k+5..7] spare
     unsigned long long *slots = nullptr;  // [instance][3][kDtSlots]
-    unsigned *tickets = nullptr;          // [instance][kDtTickets + 1]
+    unsigned *tickets = nullptr;          // [instance][kDtTickets + 1][kDtTicketStride]
     int n_inst = 1;          // instances (ensembles); > 1: inst and chunk are set
     int32_t *inst = nullptr;    // [K] instance of each internal element
     void *chunk = nullptr;      // [nchunks] DtChunk: element chunks of the time-step pass (never across instances)

@@ -1098,8 +1098,9 @@ int upload_mesh_impl(esdg_ctx *ctx, int N, int64_t K, const double *x, const dou
     TRY(alloc(ctx, &B.count, sizeof(int)));
     TRY(alloc(ctx, &B.dscal, 8 * ni * sizeof(double)));
     TRY(alloc(ctx, &B.slots, (size_t)3 * kDtSlots * ni * sizeof(unsigned long long)));
-    TRY(alloc(ctx, &B.tickets, (size_t)(kDtTickets + 1) * ni * sizeof(unsigned)));
-    CK(hipMemsetAsync(B.tickets, 0, (size_t)(kDtTickets + 1) * ni * sizeof(unsigned), ctx->stream));
+    const size_t ticket_bytes = (size_t)(kDtTickets + 1) * kDtTicketStride * ni * sizeof(unsigned);
+    TRY(alloc(ctx, &B.tickets, ticket_bytes));
+    CK(hipMemsetAsync(B.tickets, 0, ticket_bytes, ctx->stream));
     // (a degree's only instance of an ensemble with the step check has them too)
     TRY(alloc(ctx, &B.iflags, ni * sizeof(int)));
     TRY(alloc(ctx, &B.imask, ni * sizeof(int)));
