@@ -2135,12 +2135,12 @@ __device__ __forceinline__ void dt_block_min(R cflb, R viscb, R posb, unsigned l
 }
 
 // Minimum over the wave of an instance's slots of one bound, which go back to
-// +inf.  The loads are atomic (past this XCD's L2).
+// +inf.  Loads and stores are atomic (past this XCD's L2).
 __device__ __forceinline__ double take_slots(unsigned long long *slots, int lane)
 {
     static_assert(kDtSlots == 64, "one slot per lane");
     const unsigned long long v = __hip_atomic_load(&slots[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    slots[lane] = 0x7FF0000000000000ull;
+    __hip_atomic_store(&slots[lane], 0x7FF0000000000000ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return wave_min(__longlong_as_double((long long)v));
 }
 
