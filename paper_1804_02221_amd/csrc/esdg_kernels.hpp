@@ -1868,12 +1868,13 @@ struct DtChunk {
     int32_t inst, index, n, pad;
 };
 
-// What the host reads of a step or of the diagnostics (pinned host memory that
-// the GPU writes).
+// What the host reads of a step, its statistics or the diagnostics (pinned host
+// memory that the GPU writes).
 struct HostStatus {
     int flags[kNumFlags];
     double time;
     double sums[8];
+    int64_t viscous;
 };
 
 // Report the flags and the time and clear the flags (all but that of the mesh).

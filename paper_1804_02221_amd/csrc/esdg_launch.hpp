@@ -32,7 +32,7 @@ struct Bufs {
     void *dtc = nullptr, *dtv = nullptr;  // [K] per-element CFL / viscous bounds of one state
     void *eps[3] = {};       // [K] element viscosity of each state buffer
     void *vfl[3] = {};       // [K][4][nf][2] own part of the viscous face fluxes of those with eps > 0
-    int *count = nullptr;    // number of elements with eps > 0 (esdg_step_stats)
+    unsigned long long *count = nullptr;  // count_viscous_kernel's counter (esdg_step_stats)
     double *dscal = nullptr; // per instance k: [8k..8k+3] dt and its bounds, [8k+4] time, [8k+5..7] spare
     unsigned long long *slots = nullptr;  // [instance][3][kDtSlots]
     unsigned *tickets = nullptr;          // [instance][kDtTickets + 1][kDtTicketStride]
