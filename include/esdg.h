@@ -268,7 +268,7 @@ int esdg_profile_read_adjoint(esdg_ctx *ctx, double *ms, int64_t *launches);
  * (viscosity of a state no stage produced), 2 and 3 none (the viscous terms
  * are part of the stage kernel), 4 time-step pass (eq. CFLConstraints and the
  * CFL/viscous bounds), 5 adjoint reverse stage.
- * esdg_profile_read's av figures are classes 1-3. */
+ * esdg_profile_read's av figures are class 1. */
 int esdg_profile_read_kernels(esdg_ctx *ctx, double ms[6], int64_t launches[6]);
 
 /*
@@ -414,11 +414,10 @@ int esdg_adjoint_forward(esdg_ctx *ctx, int nsteps, double dt, int every, const 
  * initial state held fixed) and, when not NULL, g{h,hu,hv}0 = seed * dL/dW(0).
  * Each segment between checkpoints is recomputed from its checkpoint (but the
  * last where the forward sweep found an earlier reverse sweep's memory to keep
- * its stages in), then its stages are reversed.  Leaves the current state alone.  ESDG_EINVAL if
- * no forward sweep is recorded or the bathymetry or the parameters changed
- * since.  (For an
- * initial state set through the surface, h(0) = H0 - b, the total gradient
- * is gb - gh0.)
+ * its stages in), then its stages are reversed.  Leaves the current state
+ * alone.  ESDG_EINVAL if no forward sweep is recorded or the bathymetry or the
+ * parameters changed since.  (For an initial state set through the surface,
+ * h(0) = H0 - b, the total gradient is gb - gh0.)
  */
 int esdg_adjoint_backward(esdg_ctx *ctx, double seed, double *gb, double *gh0, double *ghu0,
                           double *ghv0, int mem);

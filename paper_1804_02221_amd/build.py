@@ -28,7 +28,8 @@ DEGREES = range(2, 9)
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-std=c++17", "-O3", "-fPIC", "--offload-arch=gfx950",
-         # packed FP32 instructions off (see DESIGN notes on the toolchain)
+         # packed FP32 instructions off: some of the forms the compiler makes
+         # of ordinary float code have given wrong results on gfx950
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", INCLUDE, "-I", CSRC]
 

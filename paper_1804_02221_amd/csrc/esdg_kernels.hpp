@@ -858,13 +858,14 @@ __device__ __forceinline__ R viscosity_from_totals(R all, R top, R allM, R topM,
 // the exact test of viscosity_from_totals would give zero too.  tau = 0
 // (thresholds near rounding, see phys()) leaves every element to that test.
 //
-// Per line N+1 LDS reads and 2(N+1) + 10 operations on 2(N+1) lanes, against
-// 4(N+1) reads, 2(N+1) multiply-adds and three reductions on every lane for
-// the transform, with which the epilogue was bound by LDS and its barriers.
-// Stage kernel on a smooth flow, with the late arguments through kernarg(): 571 -> 541 us at N = 7,
-// 512^2 (float32, 384^2: 214 -> 192 us), 107 -> 91 us at N = 5, 255^2, 152 ->
-// 139 us at N = 2, 601^2.  Tiles at wet/dry fronts pay for both tests: 23.2 ->
-// 23.1 us on a 200^2, N = 3 mesh of which a twentieth is such.
+// Per line N+1 LDS reads and about 4(N+1) + 6 operations (eight per mirrored
+// pair of nodes) on 2(N+1) lanes, against 4(N+1) reads, 2(N+1) multiply-adds
+// and three reductions on every lane for the transform, with which the
+// epilogue was bound by LDS and its barriers.  The stage kernel of a smooth
+// flow took 5% less for it at N = 7, 512^2 (float32, 384^2: 10%), 15% at N = 5,
+// 255^2, 9% at N = 2, 601^2 (571, 214, 107 and 152 us before).  Tiles at
+// wet/dry fronts pay for both tests: even on a 200^2, N = 3 mesh of which a
+// twentieth is such.
 template <int N, typename R>
 __device__ __forceinline__ bool smooth_line(const R *sh, int l, const Uni<R> &tab, R tau)
 {
@@ -1282,11 +1283,10 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
     // Node el*np + p of the tile is lane t's: every field is read and written
     // at its tile's start (a scalar) plus the one lane offset, which lanes
     // without a node of their own set to the tile's first node (their values
-    // are never stored or summed).  With one 64-bit address per field and
-    // lane, masked loads and a table load behind the face slots' the kernel
-    // took 548 us (now 536) at N = 7, 512^2, 36.4 (33.7) at 128^2, 92 (88) at
-    // N = 5, 255^2, 138 (133) at N = 2, 601^2, and in single precision 193
-    // (183) at N = 7, 384^2.
+    // are never stored or summed).  One 64-bit address per field and lane,
+    // masked loads and a table load behind the face slots' cost 2% at N = 7,
+    // 512^2 (548 us), 8% at 128^2, 5% at N = 5, 255^2, 4% at N = 2, 601^2, and
+    // in single precision 5% at N = 7, 384^2.
     const int64_t q0 = e0 * np;
     const uint32_t tq = act ? (uint32_t)t : 0u;
     const Phys<R> &P = a.P;
@@ -1462,10 +1462,10 @@ __global__ __launch_bounds__((StageCfg<N, V>::T), (StageWaves<N, R, MODE, V>::va
         // d dhv and d dh meet pA and pC after the loop (Hu, Hv, H), so that A1,
         // C2 and C3 are not rounded at full size per partner.  22 operations a
         // partner, against 27 with the jumps of A and C and their sums; this
-        // kernel is bound by vector instructions.  N = 7, 512^2: a stage
-        // 303 us; the right-hand side's mass error 7.4e-7 -> 6.3e-7 of its
-        // maximum (N = 8: 8.2e-7 -> 5.1e-7).  With e and dh sA summed as they
-        // are it is 18 operations and 296 us, but errors of 1.1e-6 for both.
+        // kernel is bound by vector instructions.  The right-hand side's mass
+        // error went from 7.4e-7 to 6.3e-7 of its maximum at N = 7, 512^2 (N =
+        // 8: 8.2e-7 to 5.1e-7).  With e and dh sA summed as they are it is 18
+        // operations and a stage 2% shorter, but errors of 1.1e-6 for both.
         const int base = el * PS;
         constexpr int VU = StageCfg<N, V>::VU32;
         // (the staged and own terms are relative to the element's middle

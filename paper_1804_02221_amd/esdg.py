@@ -379,7 +379,8 @@ class Solver:
 
     def profile_read_kernels(self):
         """Summed event milliseconds and launch counts per kernel class since
-        the last read (then reset): {class: (ms, launches)}."""
+        the last read (then reset): {class: (ms, launches)}.  The viscous
+        classes stay empty: their terms are part of the stage kernel."""
         ms = np.zeros(6)
         n = np.zeros(6, dtype=np.int64)
         self._check(lib().esdg_profile_read_kernels(self._ctx, ms.ctypes.data_as(C.c_void_p),
