@@ -1870,7 +1870,7 @@ struct DtChunk {
 
 // What the host reads of a step, its statistics or the diagnostics (pinned host
 // memory that the GPU writes).
-struct HostStatus {
+struct alignas(128) HostStatus {
     int flags[kNumFlags];
     double time;
     double sums[8];
