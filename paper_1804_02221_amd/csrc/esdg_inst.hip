@@ -223,7 +223,7 @@ hipError_t Launch<N, R>::dt(const Bufs &B, int in, bool av, bool fused, int mode
     }
     // kDtUnroll face nodes per thread before a workgroup takes a second round
     // (one per thread, the rest of the unroll clamped away, took 15 us at
-    // 524288 face nodes and 4.7 more to reduce the minima; now 11.6 in all)
+    // 524288 face nodes and 4.7 more to reduce the minima; now 10 in all)
     constexpr int64_t np = (N + 1) * (N + 1), per = (int64_t)kDtThreads * kXcds;
     const bool faces = P.limiter_on && mode != kDtCheck;
     const int64_t nfn = faces ? (B.K * 4 * (N + 1) + kDtUnroll - 1) / kDtUnroll : 0;

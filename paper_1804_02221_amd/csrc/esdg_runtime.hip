@@ -1193,7 +1193,7 @@ int upload_mesh_impl(esdg_ctx *ctx, int N, int64_t K, const double *x, const dou
         // (about 2048 chunks of at most 256 and at least 8 elements: fewer,
         // larger ones left most of the chip idle and walked their face nodes
         // one after the other, 20-33 us where 12 meshes of 16^2 to 64^2
-        // elements now take 13)
+        // elements now take 10)
         const int64_t per = std::max<int64_t>(8, std::min<int64_t>(256, K / kDtMaxBlocks));
         std::vector<DtChunk> chunks;
         for (int k = 0; k < ni; ++k) {
