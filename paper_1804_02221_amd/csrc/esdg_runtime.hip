@@ -9,6 +9,7 @@
 #include <algorithm>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <string>
 #include <type_traits>
 #include <vector>
@@ -303,7 +304,8 @@ public:
 // (never destroyed: a context may outlive the library's other static objects)
 StatusBlocks &status_blocks()
 {
-    static StatusBlocks *const s = new StatusBlocks;
+    alignas(StatusBlocks) static unsigned char room[sizeof(StatusBlocks)];
+    static StatusBlocks *const s = new (room) StatusBlocks;
     return *s;
 }
 
